@@ -11,13 +11,14 @@
 // Kernels, all deterministic (no atomics):
 //   bwd_pre    per (sequence, head, row): LSE in log2 units and -D, in two
 //              planes whose rows are padded to a multiple of 64 (zeros)
-//   bwd_kv     key-stationary, dV and dK together: a workgroup owns 128 keys
+//   bwd_main   the two passes, each workgroup one unit of either:
+//     bwd_dq   query-stationary: like the forward, a workgroup owns 256
+//              rows of one query head and sweeps the keys up to the diagonal
+//     bwd_kv   key-stationary, dV and dK together: a workgroup owns 128 keys
 //              of one kv head and sweeps the query rows at or after them (one
 //              row chunk of them), for every query head of the GQA group,
 //              accumulating in registers
 //   bwd_reduce sums the row-chunk partials of dK and dV in chunk order
-//   bwd_dq     query-stationary: like the forward, a workgroup owns 256
-//              rows of one query head and sweeps the keys up to the diagonal
 // gfx950 mapping
 //   * v_mfma_f32_32x32x16_bf16 with fp32 accumulation.  The operand order
 //     puts every elementwise step (P, dS) in the accumulator layout and feeds
@@ -117,6 +118,34 @@ __global__ __launch_bounds__(kPreThreads) void bwd_pre_kernel(
   }
 }
 
+// ---------------------------------------------------------------- arguments
+// Q, K, V and dO as the passes read them: one local buffer each.
+struct LocalRows {
+  const uint16_t *p;
+  uint32_t rows, row_elems;
+};
+inline LocalRows local_rows(const RowView &v) {
+  return LocalRows{static_cast<const uint16_t *>(v.p[0]), v.rows, v.row_elems};
+}
+// Row r of (beta, head h), and in `left` the sequence's rows from r on.
+__device__ __forceinline__ const uint16_t *local_row(const LocalRows &v, int beta, uint32_t r,
+                                                     int h, int d, uint32_t &left) {
+  left = v.rows - r;
+  return v.p + (((size_t)beta * v.rows + r) * v.row_elems + (size_t)h * d);
+}
+
+struct BwdArgs {
+  LocalRows q, k, v, d_o;
+  RowView dq, dk, dv;     // outputs (dk, dv: the partial sums when there are several)
+  const float *lp, *np;   // the LSE2 and -D planes
+  size_t chunk_elems;     // from one partial sum of dk or dv to the next
+  uint32_t plane_bytes;   // np - lp
+  uint32_t dq_blocks;     // workgroups of the dQ pass
+  int b, S, Sp, Hl, Hkl, n_rep;
+  int nchunks, chunk_tiles;
+  float c, scale;         // scale * log2(e), scale
+};
+
 // ------------------------------------------------------ bwd_kv (dV and dK)
 // Key-stationary, dV and dK in one pass.  A workgroup of 8 waves, two per
 // SIMD, owns 128 keys of one kv head and sweeps 64-row query steps for all
@@ -150,34 +179,35 @@ struct KvCfg {
   static constexpr int DMA_PER_WAVE = kQM * CPR / kKvThreads;     // 1 KB copies per tile
   static constexpr int KV_DMA_PER_WAVE = kKN * CPR / kKvThreads;  // for the V tile
   static constexpr bool V_REGS = D < 128;  // V of the wave's keys fits in registers
-};
-
-template <int D, bool SH>
-__global__ __launch_bounds__(kKvThreads, 1) void bwd_kv_kernel(
-    const RowView qv, const RowView kv, const RowView vv, const RowView dov,
-    const float *__restrict__ lp, uint32_t plane_bytes /* np - lp */, const RowView dvv,
-    const RowView dkv, size_t chunk_elems, int S, int Sp, int Hl, int Hkl, int n_rep,
-    int kvheads_total, int ktiles, int nchunks, int chunk_tiles, float c /* scale*log2e */,
-    float dk_scale) {
-  using C = KvCfg<D>;
-  using T = LdsTile<C::LW>;
   // LDS: Q tiles of the two ring stages, their dO tiles, their (LSE2, -D)
   // blocks, then (d = 128) the V tile of the workgroup's keys.  After the
   // last step the same bytes hold the second waves' partial sums: 1 KB per
   // (key block, tensor, register group).
-  constexpr int kDoRegion = 2 * C::TILE_BYTES;
-  constexpr int kAuxRegion = 4 * C::TILE_BYTES;
-  constexpr int kKvRegion = kAuxRegion + 2 * C::AUX_BYTES;
-  constexpr int kPartBytes = kKvWaves / 2 * 2 * C::NE * 4 * 1024;
-  constexpr int kRingBytes = kKvRegion + (C::V_REGS ? 0 : C::KT_BYTES);
-  constexpr int kLdsBytes = kRingBytes > kPartBytes ? kRingBytes : kPartBytes;
-  __shared__ __attribute__((aligned(16))) unsigned char smem[kLdsBytes];
+  static constexpr int DO_REGION = 2 * TILE_BYTES;
+  static constexpr int AUX_REGION = 4 * TILE_BYTES;
+  static constexpr int KV_REGION = AUX_REGION + 2 * AUX_BYTES;
+  static constexpr int PART_BYTES = kKvWaves / 2 * 2 * NE * 4 * 1024;
+  static constexpr int RING_BYTES = KV_REGION + (V_REGS ? 0 : KT_BYTES);
+  static constexpr int LDS_BYTES = RING_BYTES > PART_BYTES ? RING_BYTES : PART_BYTES;
+};
+
+template <int D, bool SH>
+__device__ __forceinline__ void bwd_kv_unit(const BwdArgs &a, int L, unsigned char *smem) {
+  using C = KvCfg<D>;
+  using T = LdsTile<C::LW>;
+  constexpr int kDoRegion = C::DO_REGION, kAuxRegion = C::AUX_REGION, kKvRegion = C::KV_REGION;
+  const LocalRows qv = a.q, kv = a.k, vv = a.v, dov = a.d_o;
+  const float *lp = a.lp;
+  const uint32_t plane_bytes = a.plane_bytes;
+  const int S = a.S, Sp = a.Sp, Hl = a.Hl, Hkl = a.Hkl, n_rep = a.n_rep;
+  const int kvheads_total = a.b * Hkl, nchunks = a.nchunks, chunk_tiles = a.chunk_tiles;
+  const int ktiles = (S + kKN - 1) / kKN;
+  const float c = a.c, dk_scale = a.scale;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kw = w & 3, h = w >> 2;  // key block, row half
   const int l32 = lane & 31, hh = lane >> 5;
-  const int L = blockIdx.x;
   const int hb = L % kvheads_total;
   int kt, ch;
   kv_unit(L / kvheads_total, nchunks, chunk_tiles, kt, ch);
@@ -199,7 +229,7 @@ __global__ __launch_bounds__(kKvThreads, 1) void bwd_kv_kernel(
   bf16x8 kf[C::NS], vf[kVRegs ? C::NS : 1];
   {
     uint32_t left;
-    const rsrc_t rk = make_rsrc(view_row<false, const uint16_t>(kv, beta, k0, kvh, D, left),
+    const rsrc_t rk = make_rsrc(local_row(kv, beta, k0, kvh, D, left),
                                 left * kv_row_bytes);
 #pragma unroll
     for (int s = 0; s < C::NS; ++s) {
@@ -207,7 +237,7 @@ __global__ __launch_bounds__(kKvThreads, 1) void bwd_kv_kernel(
       kf[s] = 2 * s < D / 8 ? as_bf16x8(buf_load16(rk, off)) : bf16x8{};  // columns past D
     }
     if constexpr (kVRegs) {
-      const rsrc_t rv = make_rsrc(view_row<false, const uint16_t>(vv, beta, k0, kvh, D, left),
+      const rsrc_t rv = make_rsrc(local_row(vv, beta, k0, kvh, D, left),
                                   left * kv_row_bytes);
 #pragma unroll
       for (int s = 0; s < C::NS; ++s) {
@@ -218,7 +248,7 @@ __global__ __launch_bounds__(kKvThreads, 1) void bwd_kv_kernel(
     wait_vmcnt<0>();  // retire the tracked loads before untracked copies start
     if constexpr (!kVRegs) {
       const u32x4 rv = make_rsrc_words(
-          view_row<false, const uint16_t>(vv, beta, k0, kvh, D, left), left * kv_row_bytes);
+          local_row(vv, beta, k0, kvh, D, left), left * kv_row_bytes);
 #pragma unroll
       for (int i = 0; i < C::KV_DMA_PER_WAVE; ++i) {
         const int pos = (w * C::KV_DMA_PER_WAVE + i) * 64 + lane;
@@ -302,16 +332,16 @@ __global__ __launch_bounds__(kKvThreads, 1) void bwd_kv_kernel(
   auto head_resources = [&]() __attribute__((always_inline)) {
     const int hq = kvh * n_rep + ld_hr;
     uint32_t left;  // rows from r_lo to the sequence's end; rows past it read as zeros
-    rq = make_rsrc_words(view_row<false, const uint16_t>(qv, beta, r_lo, hq, D, left),
+    rq = make_rsrc_words(local_row(qv, beta, r_lo, hq, D, left),
                          left * q_row_bytes);
-    rd = make_rsrc_words(view_row<false, const uint16_t>(dov, beta, r_lo, hq, D, left),
+    rd = make_rsrc_words(local_row(dov, beta, r_lo, hq, D, left),
                          left * q_row_bytes);
     ra = make_rsrc_words(lp + ((size_t)beta * Hl + hq) * Sp, plane_bytes + (uint32_t)Sp * 4);
   };
   auto advance = [&](u32x4 &r, uint32_t bytes) __attribute__((always_inline)) {
-    const uint64_t a = (((uint64_t)r[1] << 32) | r[0]) + bytes;  // 48-bit base, stride 0
-    r[0] = (uint32_t)a;
-    r[1] = (uint32_t)(a >> 32);
+    const uint64_t base = (((uint64_t)r[1] << 32) | r[0]) + bytes;  // 48-bit base, stride 0
+    r[0] = (uint32_t)base;
+    r[1] = (uint32_t)(base >> 32);
     r[2] -= bytes;  // rows left from the new first row (at least one)
   };
   head_resources();
@@ -342,11 +372,11 @@ __global__ __launch_bounds__(kKvThreads, 1) void bwd_kv_kernel(
   // 16 values (rows 32h + 8g + 4hh + {0..3} of the step) of part `part`
   // (0: LSE2, 1: -D) of stage stg's aux block.
   auto aux_rows = [&](int stg, int part) __attribute__((always_inline)) {
-    const unsigned char *a = smem + aux_lane + stg * C::AUX_BYTES + 256 * part;
+    const unsigned char *src = smem + aux_lane + stg * C::AUX_BYTES + 256 * part;
     f32x16 v;
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-      const f32x4 x = *reinterpret_cast<const f32x4 *>(a + 4 * 8 * g);
+      const f32x4 x = *reinterpret_cast<const f32x4 *>(src + 4 * 8 * g);
 #pragma unroll
       for (int y = 0; y < 4; ++y) v[4 * g + y] = x[y];
     }
@@ -470,10 +500,10 @@ __global__ __launch_bounds__(kKvThreads, 1) void bwd_kv_kernel(
   __syncthreads();
   if (h == 1 || key >= S) return;
   uint32_t left;
-  float *ov = view_row<true, float>(dvv, beta, k0, kvh, D, left) + (size_t)ch * chunk_elems +
-              (size_t)(key - k0) * dvv.row_elems;
-  float *ok = view_row<true, float>(dkv, beta, k0, kvh, D, left) + (size_t)ch * chunk_elems +
-              (size_t)(key - k0) * dkv.row_elems;
+  float *ov = view_row<true, float>(a.dv, beta, k0, kvh, D, left) + (size_t)ch * a.chunk_elems +
+              (size_t)(key - k0) * a.dv.row_elems;
+  float *ok = view_row<true, float>(a.dk, beta, k0, kvh, D, left) + (size_t)ch * a.chunk_elems +
+              (size_t)(key - k0) * a.dk.row_elems;
 #pragma unroll
   for (int n = 0; n < C::NE; ++n)
 #pragma unroll
@@ -536,23 +566,23 @@ struct DqCfg {
   static constexpr int DMA_PER_WAVE = kDQN * CPR / kDqThreads;
 };
 
+// LDS: the K tiles of the kStages ring stages, then their V tiles; with the
+// tile loop unrolled over the stages every operand address is a lane's fixed
+// offset plus an instruction immediate.
 template <int D, bool SH>
-__global__ __launch_bounds__(kDqThreads, 1) void bwd_dq_kernel(
-    const RowView qv, const RowView kv, const RowView vv, const RowView dov,
-    const float *__restrict__ lp, const float *__restrict__ np, const RowView dqv, int S, int Sp,
-    int Hl, int n_rep, int heads_total, int qtiles, float c, float scale) {
+__device__ __forceinline__ void bwd_dq_tile(const BwdArgs &a, int L, unsigned char *smem) {
   using C = DqCfg<D>;
   using T = LdsTile<C::LW>;
-  // LDS: the K tiles of the kStages ring stages, then their V tiles; with
-  // the tile loop unrolled over the stages every operand address is a lane's
-  // fixed offset plus an instruction immediate.
-  __shared__ __attribute__((aligned(16))) unsigned char smem[kStages * C::STAGE_BYTES];
   constexpr int kVRegion = kStages * C::TILE_BYTES;
+  const LocalRows qv = a.q, kv = a.k, vv = a.v, dov = a.d_o;
+  const float *lp = a.lp, *np = a.np;
+  const int S = a.S, Sp = a.Sp, Hl = a.Hl, n_rep = a.n_rep, heads_total = a.b * Hl;
+  const int qtiles = (S + kDQM - 1) / kDQM;
+  const float c = a.c, scale = a.scale;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hh = lane >> 5;
-  const int L = blockIdx.x;
   const int qt = qtiles - 1 - L / heads_total;
   const int hb = L % heads_total;
   const int beta = hb / Hl, h = hb % Hl, kvh = h / n_rep;
@@ -563,14 +593,14 @@ __global__ __launch_bounds__(kDqThreads, 1) void bwd_dq_kernel(
   const uint32_t q_row_bytes = qv.row_elems * 2, kv_row_bytes = kv.row_elems * 2;
   uint32_t left;
   const rsrc_t rq =
-      make_rsrc(view_row<false, const uint16_t>(qv, beta, q0, h, D, left), left * q_row_bytes);
+      make_rsrc(local_row(qv, beta, q0, h, D, left), left * q_row_bytes);
   const rsrc_t rd =
-      make_rsrc(view_row<false, const uint16_t>(dov, beta, q0, h, D, left), left * q_row_bytes);
+      make_rsrc(local_row(dov, beta, q0, h, D, left), left * q_row_bytes);
   // K and V are local (the in-place entry point packs them): one resource
   // per head for every tile.
-  const u32x4 rk = make_rsrc_words(view_row<false, const uint16_t>(kv, beta, 0, kvh, D, left),
+  const u32x4 rk = make_rsrc_words(local_row(kv, beta, 0, kvh, D, left),
                                    left * kv_row_bytes);
-  const u32x4 rv = make_rsrc_words(view_row<false, const uint16_t>(vv, beta, 0, kvh, D, left),
+  const u32x4 rv = make_rsrc_words(local_row(vv, beta, 0, kvh, D, left),
                                    left * kv_row_bytes);
   const uint32_t smem_lds = lds_addr_of(smem);
 
@@ -742,17 +772,37 @@ __global__ __launch_bounds__(kDqThreads, 1) void bwd_dq_kernel(
   }
 
   if (row < S) {
-    float *dqr = view_row<SH, float>(dqv, beta, q0, h, D, left) + (size_t)(row - q0) * dqv.row_elems;
+    float *dqr = view_row<SH, float>(a.dq, beta, q0, h, D, left) + (size_t)(row - q0) * a.dq.row_elems;
 #pragma unroll
     for (int n = 0; n < C::NE; ++n)
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         if (32 * n + 8 * g >= D) continue;  // padding columns
-        f32x4 a = {qacc[n][4 * g] * scale, qacc[n][4 * g + 1] * scale,
-                   qacc[n][4 * g + 2] * scale, qacc[n][4 * g + 3] * scale};
-        *reinterpret_cast<f32x4 *>(dqr + 32 * n + 8 * g + 4 * hh) = a;
+        *reinterpret_cast<f32x4 *>(dqr + 32 * n + 8 * g + 4 * hh) =
+            f32x4{qacc[n][4 * g] * scale, qacc[n][4 * g + 1] * scale, qacc[n][4 * g + 2] * scale,
+                  qacc[n][4 * g + 3] * scale};
       }
   }
+}
+
+// ---------------------------------------------------------------- bwd_main
+// Both passes in one launch: neither reads what the other writes, so the dQ
+// tiles (heaviest first) and then the key units (full ones, then the diagonal
+// ones, longest first) form one list, and the short units at its end fill the
+// CUs that the long ones leave idle.  Workgroups [0, dq_blocks) take dQ tiles.
+// Each pass alone leaves most CUs idle while its longest workgroups finish, up
+// to S = 16K with 8 query heads (one workgroup per CU, or fewer).  One launch
+// against two, the whole step on one MI355X: 8 heads of 128, S = 8K 740 -> 672
+// us; 8 heads, b*S = 2 x 2K 291 -> 232 us; 16K and more: within 1%.
+template <int D, bool SH>
+__global__ __launch_bounds__(kKvThreads, 1) void bwd_main_kernel(const BwdArgs a) {
+  static_assert(kKvThreads == kDqThreads, "one workgroup size for both passes");
+  constexpr int kKvLds = KvCfg<D>::LDS_BYTES, kDqLds = kStages * DqCfg<D>::STAGE_BYTES;
+  __shared__ __attribute__((aligned(16))) unsigned char smem[kKvLds > kDqLds ? kKvLds : kDqLds];
+  if (blockIdx.x < a.dq_blocks)
+    bwd_dq_tile<D, SH>(a, (int)blockIdx.x, smem);
+  else
+    bwd_kv_unit<D, SH>(a, (int)(blockIdx.x - a.dq_blocks), smem);
 }
 
 template <int D, bool SH>
@@ -774,39 +824,34 @@ hipError_t launch_bwd_d(const RowView &q, const RowView &k, const RowView &v, co
   hipLaunchKernelGGL((bwd_pre_kernel<D, SH>), dim3((unsigned)pre_blocks), dim3(kPreThreads), 0,
                      stream, o, d_o, lse, lp, np, rows, s.S, Sp, s.Hl);
 
-  const int ktiles = (s.S + kKN - 1) / kKN;
   const int kvheads_total = s.b * s.Hkl;
   const BwdChunks ck = bwd_chunks(s);
-  const dim3 kv_grid((unsigned)(ck.units * kvheads_total));
-  RowView dv_out = dv, dk_out = dk;
-  size_t chunk_elems = 0;
+  BwdArgs a{local_rows(q), local_rows(k), local_rows(v), local_rows(d_o), dq, dk, dv};
+  a.lp = lp, a.np = np, a.plane_bytes = plane_bytes;
+  a.b = s.b, a.S = s.S, a.Sp = Sp, a.Hl = s.Hl, a.Hkl = s.Hkl, a.n_rep = n_rep;
+  a.nchunks = ck.n, a.chunk_tiles = ck.T;
+  a.c = c, a.scale = s.scale;
   float *dv_part = nullptr, *dk_part = nullptr;
   if (ck.n > 1) {  // partial sums in the workspace, reduced below
-    chunk_elems = (size_t)kvheads_total * s.S * D;
+    a.chunk_elems = (size_t)kvheads_total * s.S * D;
     dv_part = ws + ck.part_offset_floats;
-    dk_part = dv_part + (size_t)ck.n * chunk_elems;
-    dv_out = local_view(dv_part, s.S, s.Hkl, D);
-    dk_out = local_view(dk_part, s.S, s.Hkl, D);
+    dk_part = dv_part + (size_t)ck.n * a.chunk_elems;
+    a.dv = local_view(dv_part, s.S, s.Hkl, D);
+    a.dk = local_view(dk_part, s.S, s.Hkl, D);
   }
-  hipLaunchKernelGGL((bwd_kv_kernel<D, SH>), kv_grid, dim3(kKvThreads), 0, stream, q, k, v, d_o,
-                     lp, plane_bytes, dv_out, dk_out, chunk_elems, s.S, Sp, s.Hl, s.Hkl, n_rep,
-                     kvheads_total, ktiles, ck.n, ck.T, c, s.scale);
+  a.dq_blocks = (uint32_t)((s.S + kDQM - 1) / kDQM * s.b * s.Hl);
+  const dim3 grid(a.dq_blocks + (unsigned)(ck.units * kvheads_total));
+  hipLaunchKernelGGL((bwd_main_kernel<D, SH>), grid, dim3(kKvThreads), 0, stream, a);
   if (ck.n > 1) {
     const uint32_t row_quads = (uint32_t)(s.Hkl * D / 4);
     const uint32_t seq_quads = (uint32_t)s.S * row_quads;
     const dim3 rg((seq_quads + kPreThreads - 1) / kPreThreads, (unsigned)s.b);
     const FastDiv by_rq = FastDiv::make(row_quads);
     hipLaunchKernelGGL(bwd_reduce_kernel, rg, dim3(kPreThreads), 0, stream, dv_part, dv,
-                       row_quads, by_rq, seq_quads, chunk_elems, D, ck.n, ck.T);
+                       row_quads, by_rq, seq_quads, a.chunk_elems, D, ck.n, ck.T);
     hipLaunchKernelGGL(bwd_reduce_kernel, rg, dim3(kPreThreads), 0, stream, dk_part, dk,
-                       row_quads, by_rq, seq_quads, chunk_elems, D, ck.n, ck.T);
+                       row_quads, by_rq, seq_quads, a.chunk_elems, D, ck.n, ck.T);
   }
-
-  const int qtiles = (s.S + kDQM - 1) / kDQM;
-  const int heads_total = s.b * s.Hl;
-  hipLaunchKernelGGL((bwd_dq_kernel<D, SH>), dim3((unsigned)(qtiles * heads_total)),
-                     dim3(kDqThreads), 0, stream, q, k, v, d_o, lp, np, dq, s.S, Sp, s.Hl,
-                     n_rep, heads_total, qtiles, c, s.scale);
   return hipGetLastError();
 }
 
