@@ -16,9 +16,9 @@
 //              rows of one query head and sweeps the keys up to the diagonal
 //     bwd_kv   key-stationary, dV and dK together: a workgroup owns 128 keys
 //              of one kv head and sweeps the query rows at or after them (one
-//              row chunk of them), for every query head of the GQA group,
-//              accumulating in registers
-//   bwd_reduce sums the row-chunk partials of dK and dV in chunk order
+//              row chunk of them), for the query heads of the GQA group (all,
+//              or one part of them), accumulating in registers
+//   bwd_reduce sums the partials of dK and dV in (chunk, part) order
 // gfx950 mapping
 //   * v_mfma_f32_32x32x16_bf16 with fp32 accumulation.  The operand order
 //     puts every elementwise step (P, dS) in the accumulator layout and feeds
@@ -138,18 +138,18 @@ struct BwdArgs {
   LocalRows q, k, v, d_o;
   RowView dq, dk, dv;     // outputs (dk, dv: the partial sums when there are several)
   const float *lp, *np;   // the LSE2 and -D planes
-  size_t chunk_elems;     // from one partial sum of dk or dv to the next
+  size_t part_elems;      // from one partial sum of dk or dv to the next
   uint32_t plane_bytes;   // np - lp
   uint32_t dq_blocks;     // workgroups of the dQ pass
   int b, S, Sp, Hl, Hkl, n_rep;
-  int nchunks, chunk_tiles;
+  int nchunks, chunk_tiles, nsplits;
   float c, scale;         // scale * log2(e), scale
 };
 
 // ------------------------------------------------------ bwd_kv (dV and dK)
 // Key-stationary, dV and dK in one pass.  A workgroup of 8 waves, two per
-// SIMD, owns 128 keys of one kv head and sweeps 64-row query steps for all
-// query heads of the GQA group.  Wave w takes keys 32 (w % 4) .. +31 and the
+// SIMD, owns 128 keys of one kv head and sweeps 64-row query steps for the
+// unit's query heads of the GQA group (bwd_chunks says how many and why).  Wave w takes keys 32 (w % 4) .. +31 and the
 // 32-row half w / 4 of every step, and forms
 //   S^T = K Q^T and dP^T = V dO^T       (K of its keys in registers; V too
 //                                        below d = 128, else from LDS)
@@ -201,6 +201,7 @@ __device__ __forceinline__ void bwd_kv_unit(const BwdArgs &a, int L, unsigned ch
   const uint32_t plane_bytes = a.plane_bytes;
   const int S = a.S, Sp = a.Sp, Hl = a.Hl, Hkl = a.Hkl, n_rep = a.n_rep;
   const int kvheads_total = a.b * Hkl, nchunks = a.nchunks, chunk_tiles = a.chunk_tiles;
+  const int nsplits = a.nsplits;
   const int ktiles = (S + kKN - 1) / kKN;
   const float c = a.c, dk_scale = a.scale;
 
@@ -208,11 +209,14 @@ __device__ __forceinline__ void bwd_kv_unit(const BwdArgs &a, int L, unsigned ch
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kw = w & 3, h = w >> 2;  // key block, row half
   const int l32 = lane & 31, hh = lane >> 5;
-  const int hb = L % kvheads_total;
+  const int hb = L % kvheads_total, u = L / kvheads_total;
   int kt, ch;
-  kv_unit(L / kvheads_total, nchunks, chunk_tiles, kt, ch);
+  kv_unit(u / nsplits, nchunks, chunk_tiles, kt, ch);
   if (kt >= ktiles) return;  // workgroup-uniform
   const int beta = hb / Hkl, kvh = hb % Hkl;
+  // Query heads [rep0, rep1) of the group: all of them, or one of nsplits parts.
+  const int part = u % nsplits;
+  const int rep0 = part * n_rep / nsplits, rep1 = (part + 1) * n_rep / nsplits;
   const int k0 = kt * kKN;
   const int chunk_rows = chunk_tiles * kKvKeys;
   const int r_lo = max(k0, ch * chunk_rows), r_hi = min(S, (ch + 1) * chunk_rows);
@@ -269,7 +273,7 @@ __device__ __forceinline__ void bwd_kv_unit(const BwdArgs &a, int L, unsigned ch
     }
 
   const int steps_per_head = (r_hi - r_lo + kQM - 1) / kQM;
-  const int nsteps = steps_per_head * n_rep;
+  const int nsteps = steps_per_head * (rep1 - rep0);
 
   uint32_t g_off[C::DMA_PER_WAVE];
 #pragma unroll
@@ -321,7 +325,7 @@ __device__ __forceinline__ void bwd_kv_unit(const BwdArgs &a, int L, unsigned ch
   // ld_i0, and rq, rd, ra are its resources (Q and dO rows from ld_i0 on,
   // the head's (LSE2, -D) planes).  They advance by one step's rows at a
   // time and are rebuilt per head, so a step costs a few scalar additions.
-  int ld_hr = 0, ld_t = 0, ld_i0 = r_lo;
+  int ld_hr = rep0, ld_t = 0, ld_i0 = r_lo;
   u32x4 rq, rd, ra;
   // Lanes 0-15 copy the step's 64 LSE2 values, lanes 16-31 its 64 -D values
   // (the padded planes hold every row the steps reach); the other lanes
@@ -362,7 +366,7 @@ __device__ __forceinline__ void bwd_kv_unit(const BwdArgs &a, int L, unsigned ch
     if (++ld_t == steps_per_head) {
       ld_t = 0;
       ld_i0 = r_lo;
-      if (++ld_hr < n_rep) head_resources();
+      if (++ld_hr < rep1) head_resources();
     } else {
       ld_i0 += kQM;
       advance(rq, kQM * q_row_bytes);
@@ -450,7 +454,7 @@ __device__ __forceinline__ void bwd_kv_unit(const BwdArgs &a, int L, unsigned ch
     if (st + 1 < nsteps) load_step(st + 1);
   };
   int st = 0;
-  for (int hr = 0; hr < n_rep; ++hr) {
+  for (int hr = rep0; hr < rep1; ++hr) {
     for (int t = 0; t < nmask_ph; ++t, ++st) {
       begin_step(st);
       const int i0 = r_lo + t * kQM;
@@ -500,9 +504,10 @@ __device__ __forceinline__ void bwd_kv_unit(const BwdArgs &a, int L, unsigned ch
   __syncthreads();
   if (h == 1 || key >= S) return;
   uint32_t left;
-  float *ov = view_row<true, float>(a.dv, beta, k0, kvh, D, left) + (size_t)ch * a.chunk_elems +
+  const size_t slot_elems = (size_t)(ch * nsplits + part) * a.part_elems;
+  float *ov = view_row<true, float>(a.dv, beta, k0, kvh, D, left) + slot_elems +
               (size_t)(key - k0) * a.dv.row_elems;
-  float *ok = view_row<true, float>(a.dk, beta, k0, kvh, D, left) + (size_t)ch * a.chunk_elems +
+  float *ok = view_row<true, float>(a.dk, beta, k0, kvh, D, left) + slot_elems +
               (size_t)(key - k0) * a.dk.row_elems;
 #pragma unroll
   for (int n = 0; n < C::NE; ++n)
@@ -521,31 +526,46 @@ __device__ __forceinline__ void bwd_kv_unit(const BwdArgs &a, int L, unsigned ch
 }
 
 // ---------------------------------------------------------------- bwd_reduce
-// dK or dV of a key = the sum of the partial sums of the row chunks that
-// exist for its key tile, added in chunk order (deterministic).  One thread
-// per 4 consecutive elements of a key's row of the rank's kv heads; grid.y is
-// the sequence.  The partials are local [chunk][b][S][Hkl][d]; the result
-// goes through the output view (the rank's heads are contiguous in a row).
+// dK or dV (grid.z) of a key = the sum of the partial sums of the row chunks
+// that exist for its key tile, each of nsplits query-head parts, added in slot
+// order (deterministic).  One thread per 4 consecutive elements of a key's row
+// of the rank's kv heads; grid.y is the sequence.  The partials are local
+// [slot][b][S][Hkl][d]; the result goes through the output view (the rank's
+// heads are contiguous in a row).
 __global__ __launch_bounds__(kPreThreads) void bwd_reduce_kernel(
-    const float *__restrict__ part, const RowView outv, uint32_t row_quads /* Hkl*D/4 */,
-    FastDiv by_row_quads, uint32_t seq_quads /* S*row_quads */, size_t slice /* b*S*Hkl*D */,
-    int d, int nchunks, int chunk_tiles) {
+    const float *__restrict__ dk_part, const float *__restrict__ dv_part, const RowView dkv,
+    const RowView dvv, uint32_t row_quads /* Hkl*D/4 */, FastDiv by_row_quads,
+    uint32_t seq_quads /* S*row_quads */, size_t part_elems /* b*S*Hkl*D */, int d, int nchunks,
+    int chunk_tiles, int nsplits) {
   const uint32_t i = blockIdx.x * kPreThreads + threadIdx.x;
   if (i >= seq_quads) return;
   const int beta = blockIdx.y;
   const uint32_t key = by_row_quads.div(i), cq = i - key * row_quads;
   const size_t e = ((size_t)beta * seq_quads + i) * 4;
   const int first = (int)(key / kKN) / chunk_tiles;  // first chunk the key tile wrote
-  f32x4 acc = *reinterpret_cast<const f32x4 *>(part + (size_t)first * slice + e);
-  for (int ch = first + 1; ch < nchunks; ++ch) {
-    const f32x4 x = *reinterpret_cast<const f32x4 *>(part + (size_t)ch * slice + e);
+  const float *part = (blockIdx.z ? dv_part : dk_part) + (size_t)first * nsplits * part_elems + e;
+  const int n = (nchunks - first) * nsplits;
+  f32x4 acc = *reinterpret_cast<const f32x4 *>(part);
+  auto add = [&](f32x4 x) __attribute__((always_inline)) {
     acc[0] += x[0];
     acc[1] += x[1];
     acc[2] += x[2];
     acc[3] += x[3];
+  };
+  int k = 1;
+  for (; k + 4 <= n; k += 4) {  // four loads in flight
+    f32x4 x[4];
+#pragma unroll
+    for (int y = 0; y < 4; ++y)
+      x[y] = *reinterpret_cast<const f32x4 *>(part + (size_t)(k + y) * part_elems);
+#pragma unroll
+    for (int y = 0; y < 4; ++y) add(x[y]);
   }
+  for (; k < n; ++k) add(*reinterpret_cast<const f32x4 *>(part + (size_t)k * part_elems));
   uint32_t left;
-  *reinterpret_cast<f32x4 *>(view_row<true, float>(outv, beta, key, 0, d, left) + 4 * cq) = acc;
+  float *row = blockIdx.z ? view_row<true, float>(dvv, beta, key, 0, d, left)
+                          : view_row<true, float>(dkv, beta, key, 0, d, left);
+  *reinterpret_cast<f32x4 *>(row + 4 * cq) = acc;
 }
 
 // ---------------------------------------------------------------- bwd_dq
@@ -829,28 +849,27 @@ hipError_t launch_bwd_d(const RowView &q, const RowView &k, const RowView &v, co
   BwdArgs a{local_rows(q), local_rows(k), local_rows(v), local_rows(d_o), dq, dk, dv};
   a.lp = lp, a.np = np, a.plane_bytes = plane_bytes;
   a.b = s.b, a.S = s.S, a.Sp = Sp, a.Hl = s.Hl, a.Hkl = s.Hkl, a.n_rep = n_rep;
-  a.nchunks = ck.n, a.chunk_tiles = ck.T;
+  a.nchunks = ck.n, a.chunk_tiles = ck.T, a.nsplits = ck.splits;
   a.c = c, a.scale = s.scale;
   float *dv_part = nullptr, *dk_part = nullptr;
-  if (ck.n > 1) {  // partial sums in the workspace, reduced below
-    a.chunk_elems = (size_t)kvheads_total * s.S * D;
+  const int parts = ck.n * ck.splits;
+  if (parts > 1) {  // partial sums in the workspace, reduced below
+    a.part_elems = (size_t)kvheads_total * s.S * D;
     dv_part = ws + ck.part_offset_floats;
-    dk_part = dv_part + (size_t)ck.n * a.chunk_elems;
+    dk_part = dv_part + (size_t)parts * a.part_elems;
     a.dv = local_view(dv_part, s.S, s.Hkl, D);
     a.dk = local_view(dk_part, s.S, s.Hkl, D);
   }
   a.dq_blocks = (uint32_t)((s.S + kDQM - 1) / kDQM * s.b * s.Hl);
-  const dim3 grid(a.dq_blocks + (unsigned)(ck.units * kvheads_total));
+  const dim3 grid(a.dq_blocks + (unsigned)(ck.units * ck.splits * kvheads_total));
   hipLaunchKernelGGL((bwd_main_kernel<D, SH>), grid, dim3(kKvThreads), 0, stream, a);
-  if (ck.n > 1) {
+  if (parts > 1) {
     const uint32_t row_quads = (uint32_t)(s.Hkl * D / 4);
     const uint32_t seq_quads = (uint32_t)s.S * row_quads;
-    const dim3 rg((seq_quads + kPreThreads - 1) / kPreThreads, (unsigned)s.b);
-    const FastDiv by_rq = FastDiv::make(row_quads);
-    hipLaunchKernelGGL(bwd_reduce_kernel, rg, dim3(kPreThreads), 0, stream, dv_part, dv,
-                       row_quads, by_rq, seq_quads, a.chunk_elems, D, ck.n, ck.T);
-    hipLaunchKernelGGL(bwd_reduce_kernel, rg, dim3(kPreThreads), 0, stream, dk_part, dk,
-                       row_quads, by_rq, seq_quads, a.chunk_elems, D, ck.n, ck.T);
+    const dim3 rg((seq_quads + kPreThreads - 1) / kPreThreads, (unsigned)s.b, 2);
+    hipLaunchKernelGGL(bwd_reduce_kernel, rg, dim3(kPreThreads), 0, stream, dk_part, dv_part, dk,
+                       dv, row_quads, FastDiv::make(row_quads), seq_quads, a.part_elems, D, ck.n,
+                       ck.T, ck.splits);
   }
   return hipGetLastError();
 }

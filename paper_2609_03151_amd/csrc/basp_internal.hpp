@@ -50,6 +50,7 @@ struct FastDiv {
 // which would otherwise grow with S squared.  Host-callable for checking.
 constexpr int kKvKeys = 128;
 constexpr int kKvMaxChunks = 16;
+constexpr int kBwdCus = 256;  // compute units the backward's units are spread over
 
 __host__ __device__ inline int kv_chunk_rows(int S) {
   int rows = (S / 4) / kKvKeys * kKvKeys;
@@ -192,35 +193,91 @@ hipError_t launch_attn_fwd(const RowView &q, const RowView &k, const RowView &v,
 
 // Workspace of the backward: the planes LSE * log2(e) and -D, each
 // [b][Hl][Sp] fp32 with Sp = S rounded up to 64 (padding rows zero), then,
-// when the key pass runs in more than one row chunk, the dV and dK partial
-// sums [chunk][b][S][Hkl][d] (fp32).  Host-callable.
+// when the key pass has more than one partial sum per key, the dV and dK
+// partial sums [slot][b][S][Hkl][d] (fp32), slot = chunk * splits + part.
+// Host-callable.
 struct BwdChunks {
-  int rows;   // rows per chunk (a multiple of kKvKeys)
-  int T;      // key tiles per chunk
-  int n;      // row chunks
-  int units;  // work units per (sequence, kv head)
+  int rows;    // rows per chunk (a multiple of kKvKeys)
+  int T;       // key tiles per chunk
+  int n;       // row chunks
+  int units;   // (key tile, row chunk) pairs per (sequence, kv head)
+  int splits;  // parts the query heads of a kv head are cut into; units each
   size_t part_offset_floats;
 };
 
 __host__ __device__ inline int bwd_plane_rows(int S) { return (S + 63) / 64 * 64; }
 
-inline BwdChunks bwd_chunks(const AttnShape &s) {
+inline size_t bwd_workspace_floats(const AttnShape &s, const BwdChunks &ck) {
+  size_t floats = ck.part_offset_floats;
+  if (ck.n * ck.splits > 1) floats += 2 * (size_t)ck.n * ck.splits * s.b * s.Hkl * s.S * s.d;
+  return floats;
+}
+
+inline BwdChunks bwd_chunks_of(const AttnShape &s, int rows, int splits) {
   BwdChunks ck;
-  ck.rows = kv_chunk_rows(s.S);
-  ck.T = ck.rows / kKvKeys;
-  ck.n = (s.S + ck.rows - 1) / ck.rows;
+  ck.rows = rows;
+  ck.T = rows / kKvKeys;
+  ck.n = (s.S + rows - 1) / rows;
   if (ck.n < 1) ck.n = 1;
   ck.units = kv_units(ck.n, ck.T);
+  ck.splits = splits;
   const size_t ld_floats = 2 * (size_t)s.b * s.Hl * bwd_plane_rows(s.S);
   ck.part_offset_floats = (ld_floats + 63) & ~(size_t)63;  // 256-byte aligned
   return ck;
 }
 
+// How the key pass is cut.  A workgroup's step is 64 rows of one query head
+// (1.3 to 1.7 us); the pass has `mean` of them per CU.  A unit much longer
+// than that leaves the other CUs idle while it runs (a kv head of 4 query
+// heads at S = 2048 is 128 steps per key tile for 8.5 per CU); a unit much
+// shorter pays its start, its 128 KB of partial sums and their reduction
+// (together about 4 steps) too often.  So a unit is about `mean` steps, below
+// 16 up to twice that, at least 8, and from 256 on half of it (measured on MI355X, backward, against
+// one unit per key tile and 2048-row chunk: 8 heads on 2 kv heads of 128, S =
+// 4096: 32-step units 133 us, 16: 145, 64: 135, unsplit 318; S = 16K:
+// 256-step units 1536 us, 512: 1576).  Query heads are split first, rows
+// next: long row chunks have fewer short diagonal units (32-step units at S =
+// 4096 as 2048 rows of one head 133 us, as 512 rows of four 142).  A unit of
+// all heads and a whole chunk of kv_chunk_rows, the old cut, stays where it is
+// no longer than that, and where the partial sums would need more than both
+// it and the static buffer of basp_attn_bwd_noalloc hold.
+inline BwdChunks bwd_chunks(const AttnShape &s) {
+  const BwdChunks whole = bwd_chunks_of(s, kv_chunk_rows(s.S), 1);
+  if (s.S < 1 || s.Hkl < 1) return whole;
+  const int n_rep = s.Hl / s.Hkl;
+  const long long ktiles = (s.S + kKvKeys - 1) / kKvKeys;
+  const long long mean = (long long)s.b * s.Hl * ktiles * (ktiles + 1) / kBwdCus;
+  long long steps = mean;
+  if (mean < 16) steps = mean < 4 ? 8 : mean < 8 ? 2 * mean : 16;
+  if (mean > 128) steps = mean < 256 ? 128 : mean / 2;
+  // Longest chunk: past S / 4 the cap of kv_chunk_rows.
+  const int cap = s.S <= 8192 ? (s.S + kKvKeys - 1) / kKvKeys * kKvKeys
+                  : kv_chunk_rows(s.S) > 8192 ? kv_chunk_rows(s.S) : 8192;
+  const long long cap_steps = cap / 64;
+  int heads = (int)(steps / cap_steps < n_rep ? steps / cap_steps : n_rep);
+  int rows = cap;
+  if (heads < 1) {  // one head of less than a whole chunk, the chunks of equal length
+    heads = 1;
+    const long long want = steps * 64;
+    const int n = (int)((s.S + want - 1) / want);
+    rows = ((s.S + n - 1) / n + kKvKeys - 1) / kKvKeys * kKvKeys;
+  }
+  const size_t whole_floats = bwd_workspace_floats(s, whole);
+  const size_t limit = whole_floats > BASP_NOALLOC_SCRATCH_BYTES / sizeof(float)
+                           ? whole_floats : BASP_NOALLOC_SCRATCH_BYTES / sizeof(float);
+  for (;; ++heads) {
+    const BwdChunks ck = bwd_chunks_of(s, rows, (n_rep + heads - 1) / heads);
+    if (bwd_workspace_floats(s, ck) <= limit) return ck;
+    if (heads >= n_rep) return whole;
+  }
+}
+
+// Never less than the whole-chunk cut takes, which can be more than the one
+// in use: so what basp_attn_bwd_noalloc takes is what that cut lets it take.
 inline size_t attn_bwd_workspace_bytes(const AttnShape &s) {
-  const BwdChunks ck = bwd_chunks(s);
-  size_t floats = ck.part_offset_floats;
-  if (ck.n > 1) floats += 2 * (size_t)ck.n * s.b * s.Hkl * s.S * s.d;
-  return floats * sizeof(float);
+  const size_t cut = bwd_workspace_floats(s, bwd_chunks(s));
+  const size_t whole = bwd_workspace_floats(s, bwd_chunks_of(s, kv_chunk_rows(s.S), 1));
+  return (cut > whole ? cut : whole) * sizeof(float);
 }
 
 // Device address of the static scratch buffer of basp_attn_bwd_noalloc

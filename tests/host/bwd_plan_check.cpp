@@ -1,0 +1,80 @@
+// Host check of the cut of the backward's key pass (bwd_chunks in
+// basp_internal.hpp), over every combination of many sequence lengths, head
+// counts, batch sizes and head dims:
+//  * chunks are whole key tiles and cover the sequence; no chunk is empty;
+//  * the query-head parts of a kv head are all non-empty and cover the heads;
+//  * the workspace holds the planes and every partial sum, is no smaller than
+//    one part per row chunk of kv_chunk_rows takes (so the static buffer's
+//    limit admits the same shapes), and no larger than both that and the
+//    static buffer;
+//  * the schedule of the chosen chunks reaches every (key tile, chunk) pair
+//    that has rows exactly once.
+// Prints the number of shapes checked; exits 1 at the first failure.
+#include <stdio.h>
+
+#include <algorithm>
+#include <set>
+#include <utility>
+#include <vector>
+
+#include "../../paper_2609_03151_amd/csrc/basp_internal.hpp"
+
+using namespace basp;
+
+static int fail(const char *what, const AttnShape &s) {
+  printf("FAIL %s: b=%d S=%d Hl=%d Hkl=%d d=%d\n", what, s.b, s.S, s.Hl, s.Hkl, s.d);
+  return 1;
+}
+
+int main() {
+  std::vector<int> lengths = {1,    64,   127,  128,  129,  255,  256,  500,   512,   1000,  1024,
+                              1500, 2047, 2048, 2049, 3000, 4096, 5000, 8191,  8192,  8193,  12345,
+                              16384, 20000, 32768, 65536, 100000, 131072, 131200, 262144, 524289};
+  int checked = 0;
+  for (int S : lengths)
+    for (int b : {1, 2, 3, 16})
+      for (int Hkl : {1, 2, 4, 8})
+        for (int n_rep : {1, 2, 3, 4, 7, 8, 64})
+          for (int d : {64, 80, 128}) {
+            const AttnShape s{b, S, Hkl * n_rep, Hkl, d, 1.f};
+            const BwdChunks ck = bwd_chunks(s);
+            if (ck.rows < kKvKeys || ck.rows % kKvKeys || ck.T * kKvKeys != ck.rows)
+              return fail("chunk rows", s);
+            if ((long long)ck.n * ck.rows < S || (long long)(ck.n - 1) * ck.rows >= S)
+              return fail("chunk count", s);
+            if (ck.n > kKvMaxChunks) return fail("more row chunks than the cap", s);
+            if (ck.splits < 1 || ck.splits > n_rep) return fail("parts", s);
+            for (int p = 0; p < ck.splits; ++p)
+              if (p * n_rep / ck.splits >= (p + 1) * n_rep / ck.splits)
+                return fail("empty part", s);
+            const size_t planes = 2 * (size_t)b * s.Hl * ((S + 63) / 64 * 64) * 4;
+            const size_t sum = (size_t)b * S * Hkl * d * 4;
+            const size_t parts = (size_t)ck.n * ck.splits;
+            const size_t need = attn_bwd_workspace_bytes(s);
+            const size_t use = planes + (parts > 1 ? 2 * parts * sum : 0);
+            const size_t n0 = (S + kv_chunk_rows(S) - 1) / kv_chunk_rows(S);
+            const size_t whole = planes + (n0 > 1 ? 2 * n0 * sum : 0);
+            if (need < use || need < whole) return fail("workspace too small", s);
+            if (need > std::max(whole, (size_t)BASP_NOALLOC_SCRATCH_BYTES) + 256)
+              return fail("workspace too large", s);
+            if (b == 1 && d == 64) {
+              const int ktiles = (S + kKvKeys - 1) / kKvKeys;
+              std::set<std::pair<int, int>> seen;
+              for (int u = 0; u < ck.units; ++u) {
+                int kt, ch;
+                kv_unit(u, ck.n, ck.T, kt, ch);
+                if (kt < ktiles && std::max(kt * kKvKeys, ch * ck.rows) < std::min(S, (ch + 1) * ck.rows) &&
+                    !seen.insert({kt, ch}).second)
+                  return fail("pair twice", s);
+              }
+              for (int kt = 0; kt < ktiles; ++kt)
+                for (int ch = 0; ch < ck.n; ++ch)
+                  if (std::max(kt * kKvKeys, ch * ck.rows) < std::min(S, (ch + 1) * ck.rows) &&
+                      !seen.count({kt, ch}))
+                    return fail("pair missing", s);
+            }
+            ++checked;
+          }
+  printf("bwd plan ok %d\n", checked);
+  return 0;
+}

@@ -1,0 +1,75 @@
+"""GPU parity at the sizes where the work of a small share is cut finer, every
+output against a plain fp64 torch computation on the GPU.
+
+The backward's key pass is cut into row chunks and query-head parts (several
+partial sums of dK and dV per key): uneven parts, ragged lengths, parts with
+one chunk, chunks with one part, b > 1, each head dim."""
+import math
+
+import pytest
+import torch
+
+import paper_2609_03151_amd as basp
+from parity import LSE_MAX_ABS, check_close, fp64_kv_head, log
+
+pytestmark = pytest.mark.gpu
+
+CASES = [  # b, S, Hl, Hkl, d
+    (1, 1024, 8, 1, 128),   # 2 chunks x 8 parts
+    (1, 1100, 7, 1, 96),    # ragged, one head per part
+    (2, 2048, 4, 1, 128),   # 2 chunks x 4 parts, b = 2
+    (1, 3000, 7, 1, 128),   # 3 chunks x 7 parts, ragged
+    (3, 769, 6, 2, 80),     # the last key tile one key long
+    (1, 2113, 3, 3, 64),    # chunks only
+    (1, 6000, 10, 2, 64),   # long ragged chunks
+    (1, 8192, 8, 2, 64),    # one chunk, parts only
+    (2, 9000, 10, 2, 128),  # uneven parts (3 and 2 heads)
+]
+
+
+def _reference(q, k, v, do, scale):
+    """O, LSE, dQ, dK, dV in fp64, one kv head of one sequence at a time."""
+    b, S, Hl, d = q.shape
+    n = Hl // k.shape[2]
+    out = [torch.empty(t.shape, dtype=torch.float64, device="cuda") for t in (q, q, k, k)]
+    lse = torch.empty((b, Hl, S), dtype=torch.float64, device="cuda")
+    for beta in range(b):
+        for h in range(k.shape[2]):
+            hq, hk = slice(h * n, (h + 1) * n), slice(h, h + 1)
+            at = slice(beta, beta + 1)
+            args = q[at, :, hq], k[at, :, hk], v[at, :, hk], do[at, :, hq]
+            o, dq, dk, dv = fp64_kv_head(*args, n, scale)
+            out[0][beta, :, hq], out[1][beta, :, hq] = o, dq
+            out[2][beta, :, h], out[3][beta, :, h] = dk, dv
+            K = k[beta, :, h].double()
+            for g in range(h * n, (h + 1) * n):
+                for r0 in range(0, S, 2048):
+                    r1 = min(S, r0 + 2048)
+                    s = (q[beta, r0:r1, g].double() @ K[:r1].T) * scale
+                    s[:, r0:].masked_fill_(torch.ones(r1 - r0, r1 - r0, dtype=torch.bool,
+                                                      device="cuda").triu_(1), -math.inf)
+                    lse[beta, g, r0:r1] = torch.logsumexp(s, dim=1)
+    return out[0], lse, out[1], out[2], out[3]
+
+
+@pytest.mark.parametrize("b,S,Hl,Hkl,d", CASES)
+def test_split_attention_matches_fp64(b, S, Hl, Hkl, d):
+    log(f"[split] b={b} S={S} Hl={Hl} Hkl={Hkl} d={d}")
+    g = torch.Generator("cuda").manual_seed(S + 31 * Hl + d)
+    mk = lambda n: torch.randn((b, S, n, d), generator=g, device="cuda").to(torch.bfloat16)
+    q, k, v, do = mk(Hl), mk(Hkl), mk(Hkl), mk(Hl)
+    scale = d ** -0.5
+    o, lse = basp.attn_fwd(q, k, v, scale=scale)
+    need = basp.attn_bwd_workspace_bytes(b, S, Hl, Hkl, d, 1)
+    # NaN everywhere the backward writes: nothing may be left out, and nothing
+    # of the workspace is read before it is written.
+    ws = torch.full(((need + 3) // 4,), math.nan, dtype=torch.float32, device="cuda")
+    grads = [torch.full(t.shape, math.nan, dtype=torch.float32, device="cuda") for t in (q, k, v)]
+    dq, dk, dv = basp.attn_bwd(q, k, v, o, lse, do, scale=scale, dq=grads[0], dk=grads[1],
+                               dv=grads[2], workspace=ws)
+    torch.cuda.synchronize()
+    ref = _reference(q, k, v, do, scale)
+    f = lambda t: t.double().cpu().numpy()
+    for name, got, want in zip(("O", "LSE", "dQ", "dK", "dV"), (o, lse, dq, dk, dv), ref):
+        bar = dict(max_abs=LSE_MAX_ABS, mean_abs=LSE_MAX_ABS) if name == "LSE" else {}
+        check_close(name, f(got), f(want), **bar)
