@@ -250,18 +250,20 @@ inline BwdChunks bwd_chunks(const AttnShape &s) {
   long long steps = mean;
   if (mean < 16) steps = mean < 4 ? 8 : mean < 8 ? 2 * mean : 16;
   if (mean > 128) steps = mean < 256 ? 128 : mean / 2;
-  // Longest chunk: past S / 4 the cap of kv_chunk_rows.
-  const int cap = s.S <= 8192 ? (s.S + kKvKeys - 1) / kKvKeys * kKvKeys
-                  : kv_chunk_rows(s.S) > 8192 ? kv_chunk_rows(s.S) : 8192;
-  const long long cap_steps = cap / 64;
-  int heads = (int)(steps / cap_steps < n_rep ? steps / cap_steps : n_rep);
-  int rows = cap;
-  if (heads < 1) {  // one head of less than a whole chunk, the chunks of equal length
-    heads = 1;
-    const long long want = steps * 64;
-    const int n = (int)((s.S + want - 1) / want);
-    rows = ((s.S + n - 1) / n + kKvKeys - 1) / kKvKeys * kKvKeys;
-  }
+  // Whole heads over the longest chunks kv_chunk_rows allows, of equal length
+  // (a short last chunk is as many units as a long one: two sequences of 8564
+  // rows, 7 heads on 1 of 128, as 8192 + 372 rows of one head 970 us, equal
+  // chunks of two heads 854 us), or, where one such unit would be too long, one
+  // head over shorter chunks.
+  const long long cap = kv_chunk_rows(s.S) > 8192 ? kv_chunk_rows(s.S) : 8192, want = steps * 64;
+  auto equal_rows = [&](long long longest) {
+    const int n = (int)((s.S + longest - 1) / longest);
+    return ((s.S + n - 1) / n + kKvKeys - 1) / kKvKeys * kKvKeys;
+  };
+  int rows = equal_rows(cap);
+  int heads = (int)((want + rows / 2) / rows < n_rep ? (want + rows / 2) / rows : n_rep);
+  if (heads <= 1 && 4 * want < 3LL * rows) rows = equal_rows(want);
+  if (heads < 1) heads = 1;
   const size_t whole_floats = bwd_workspace_floats(s, whole);
   const size_t limit = whole_floats > BASP_NOALLOC_SCRATCH_BYTES / sizeof(float)
                            ? whole_floats : BASP_NOALLOC_SCRATCH_BYTES / sizeof(float);
