@@ -13,7 +13,8 @@
 //              planes whose rows are padded to a multiple of 64 (zeros)
 //   bwd_main   the two passes, each workgroup one unit of either:
 //     bwd_dq   query-stationary: like the forward, a workgroup owns 256
-//              rows of one query head and sweeps the keys up to the diagonal
+//              rows (128 or 64 on small shares) of one query head and sweeps
+//              the keys up to the diagonal
 //     bwd_kv   key-stationary, dV and dK together: a workgroup owns 128 keys
 //              of one kv head and sweeps the query rows at or after them (one
 //              row chunk of them), for the query heads of the GQA group (all,
@@ -28,7 +29,8 @@
 //     and dS.
 //   * the streamed tiles (and, for bwd_kv, the rows' LSE2 and -D) are
 //     copied HBM -> LDS by buffer loads that write LDS directly (rows past S
-//     arrive as zeros): bwd_dq into a ring of four stages, two tiles ahead;
+//     arrive as zeros): bwd_dq into a ring of four stages, two tiles ahead
+//     (two stages, one ahead, with 128-key tiles of 128-wide rows);
 //     bwd_kv into two stages, one step ahead (measured as fast, and its
 //     unmasked loop then runs two steps per iteration, one per stage, so
 //     every LDS address is a lane offset plus an immediate).  Each wave
@@ -55,7 +57,6 @@ namespace {
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kPreThreads = 256;
-constexpr int kStages = 4;
 // Instruction classes of __builtin_amdgcn_sched_group_barrier.
 constexpr int kSchedMfma = 0x008;
 constexpr int kSchedDsRead = 0x100;
@@ -571,28 +572,38 @@ __global__ __launch_bounds__(kPreThreads) void bwd_reduce_kernel(
 // ---------------------------------------------------------------- bwd_dq
 constexpr int kDqWaves = 8;
 constexpr int kDqThreads = 64 * kDqWaves;
-constexpr int kDQM = 32 * kDqWaves;  // query rows per workgroup (32 per wave)
-constexpr int kDQN = 64;             // keys per tile
 
-template <int D>
+// The 8 waves are R row groups of 32 query rows times P = 8 / R key parts.
+// With R = 8 a wave takes every key of the 64-key tiles; else part p takes
+// keys 32p .. 32p+31 of each tile of 32 P keys, and the parts' dQ are added
+// once, through LDS, at the end: the same two waves per SIMD and products per
+// tile, for a half or a quarter of the rows and of the key loop's length.
+template <int D, int R>
 struct DqCfg {
   static constexpr int DC = HeadDim<D>::DC;
   static constexpr int LW = HeadDim<D>::LW;
-  static constexpr int TILE_BYTES = kDQN * LW * 2;
+  static constexpr int P = kDqWaves / R;
+  static constexpr int BM = 32 * R;                  // query rows per workgroup
+  static constexpr int BN = P == 1 ? 64 : 32 * P;    // keys per tile
+  static constexpr int HALVES = P == 1 ? 2 : 1;      // 32-key halves per wave and tile
+  static constexpr int TILE_BYTES = BN * LW * 2;
   static constexpr int STAGE_BYTES = 2 * TILE_BYTES;  // K, V
+  static constexpr int STAGES = STAGE_BYTES > 32768 ? 2 : 4;
   static constexpr int NS = DC / 16;
   static constexpr int NE = DC / 32;
   static constexpr int CPR = LW / 8;
-  static constexpr int DMA_PER_WAVE = kDQN * CPR / kDqThreads;
+  static constexpr int DMA_PER_WAVE = BN * CPR / kDqThreads;
+  static_assert((P - 1) * R * NE * 4096 <= STAGES * STAGE_BYTES, "parts' dQ fit the ring");
 };
 
-// LDS: the K tiles of the kStages ring stages, then their V tiles; with the
+// LDS: the K tiles of the ring stages, then their V tiles; with the
 // tile loop unrolled over the stages every operand address is a lane's fixed
 // offset plus an instruction immediate.
-template <int D, bool SH>
+template <int D, bool SH, int R>
 __device__ __forceinline__ void bwd_dq_tile(const BwdArgs &a, int L, unsigned char *smem) {
-  using C = DqCfg<D>;
+  using C = DqCfg<D, R>;
   using T = LdsTile<C::LW>;
+  constexpr int kStages = C::STAGES, kDQM = C::BM, kDQN = C::BN;
   constexpr int kVRegion = kStages * C::TILE_BYTES;
   const LocalRows qv = a.q, kv = a.k, vv = a.v, dov = a.d_o;
   const float *lp = a.lp, *np = a.np;
@@ -607,7 +618,8 @@ __device__ __forceinline__ void bwd_dq_tile(const BwdArgs &a, int L, unsigned ch
   const int hb = L % heads_total;
   const int beta = hb / Hl, h = hb % Hl, kvh = h / n_rep;
   const int q0 = qt * kDQM;
-  const int wrow0 = q0 + 32 * w;
+  const int rg = w % R, part = w / R;  // row group, key part
+  const int wrow0 = q0 + 32 * rg;
   const int row = wrow0 + l32;
 
   const uint32_t q_row_bytes = qv.row_elems * 2, kv_row_bytes = kv.row_elems * 2;
@@ -665,6 +677,7 @@ __device__ __forceinline__ void bwd_dq_tile(const BwdArgs &a, int L, unsigned ch
       buf_load16_lds_async(rv, base + g_off[i], lds + kVRegion);
     }
   };
+  const int part_off = part * 32 * T::ROW_BYTES;  // first row of the wave's keys
   // Row l32 (+32 for m = 1), chunk 2s + hh, of the K tile (a_off) and the V
   // tile (v_off).  With 64-wide rows the V region starts within reach of the
   // instruction immediate, so V takes the K offsets.
@@ -672,7 +685,7 @@ __device__ __forceinline__ void bwd_dq_tile(const BwdArgs &a, int L, unsigned ch
   int a_off[C::NS], v_off[C::NS];
 #pragma unroll
   for (int s = 0; s < C::NS; ++s) {
-    a_off[s] = T::off(l32, 2 * s + hh);
+    a_off[s] = T::off(l32, 2 * s + hh) + part_off;
     asm volatile("" : "+v"(a_off[s]));
     if constexpr (!kVImm) {
       v_off[s] = a_off[s] + kVRegion;
@@ -689,7 +702,8 @@ __device__ __forceinline__ void bwd_dq_tile(const BwdArgs &a, int L, unsigned ch
   for (int n = 0; n < C::NE; ++n)
 #pragma unroll
     for (int x = 0; x < 2; ++x) {
-      t_off[n][x] = tr_piece_off<C::LW>(4 * hh + 8 * x, 32 * n + 16 * ((lane >> 4) & 1), lane);
+      t_off[n][x] =
+          tr_piece_off<C::LW>(4 * hh + 8 * x, 32 * n + 16 * ((lane >> 4) & 1), lane) + part_off;
       asm volatile("" : "+v"(t_off[n][x]));
     }
 
@@ -699,17 +713,17 @@ __device__ __forceinline__ void bwd_dq_tile(const BwdArgs &a, int L, unsigned ch
 #pragma unroll
     for (int r = 0; r < 16; ++r) qacc[n][r] = 0.f;
 
-  // One 64-key tile in two 32-key halves (keeps the score state at 2 x 16
-  // registers).  S^T = K Q^T and dP^T = V dO^T: M = 32 keys, N = this wave's
+  // The wave's keys of one tile in 32-key halves (keeps the score state at
+  // 2 x 16 registers).  S^T = K Q^T and dP^T = V dO^T: M = 32 keys, N = this wave's
   // rows; sacc[r] holds key j0 + 32m + 8(r/4) + 4hh + r%4, query row `row`.
   // `st` = t % kStages (a constant in the unrolled loop).
   auto tile = [&](int t, int st, auto mask_tag) __attribute__((always_inline)) {
     constexpr bool MASK = decltype(mask_tag)::value;
-    const int j0 = t * kDQN;
+    const int j0 = t * kDQN + 32 * part;
     const unsigned char *Ks = smem + st * C::TILE_BYTES;
     const unsigned char *Vs = Ks;  // v_at adds the V region's base
 #pragma unroll
-    for (int m = 0; m < 2; ++m) {
+    for (int m = 0; m < C::HALVES; ++m) {
       if (MASK && j0 + 32 * m > wrow0 + 31) continue;  // wave-uniform: half entirely masked
       f32x16 sacc, pacc;
       {
@@ -760,24 +774,29 @@ __device__ __forceinline__ void bwd_dq_tile(const BwdArgs &a, int L, unsigned ch
     }
   };
   auto step = [&](int t) __attribute__((always_inline)) {
-    // Stage (t+2) % 4 last held tile t-2, finished by every wave before the
-    // barrier of iteration t-1.  With two tiles in flight the wait keeps
-    // them; the last two tiles wait for every copy.
-    if (t + 2 < nt) {
-      load_tile(t + 2);
-      wait_vmcnt<4 * C::DMA_PER_WAVE>();
-    } else {
+    if constexpr (kStages == 4) {
+      // Stage (t+2) % 4 last held tile t-2, finished by every wave before the
+      // barrier of iteration t-1.  With two tiles in flight the wait keeps
+      // them; the last two tiles wait for every copy.
+      if (t + 2 < nt) {
+        load_tile(t + 2);
+        wait_vmcnt<4 * C::DMA_PER_WAVE>();
+      } else {
+        wait_vmcnt<0>();
+      }
+      barrier_no_fence();
+    } else {  // two stages: tile t+1's stage is free once every wave is past the barrier
       wait_vmcnt<0>();
+      barrier_no_fence();
+      if (t + 1 < nt) load_tile(t + 1);
     }
-    barrier_no_fence();
   };
-  for (int t = 0; t < 2 && t < nt; ++t) load_tile(t);
+  for (int t = 0; t < kStages / 2 && t < nt; ++t) load_tile(t);
   const int t_mask = min(nt, q0 / kDQN);  // tiles before t_mask need no mask
-  static_assert(kStages == 4, "the unrolled loop assumes four ring stages");
   int t = 0;
-  for (; t + 4 <= t_mask; t += 4) {  // t % 4 == 0
+  for (; t + kStages <= t_mask; t += kStages) {  // t % kStages == 0
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < kStages; ++u) {
       step(t + u);
       tile(t + u, u, std::false_type{});
     }
@@ -791,6 +810,35 @@ __device__ __forceinline__ void bwd_dq_tile(const BwdArgs &a, int L, unsigned ch
     if (t * kDQN <= wrow0 + 31) tile(t, t % kStages, std::true_type{});  // wave-uniform
   }
 
+  if constexpr (C::P > 1) {
+    // The parts' sums: parts 1 .. P-1 put theirs in LDS (every copy landed,
+    // nothing left to read), part 0 adds them in order.  Slot of (part, row
+    // group, register group): 1 KB, lane l's 16 bytes at 16 l.
+    auto slot = [&](int p, int n, int g) __attribute__((always_inline)) {
+      return smem + ((((p - 1) * R + rg) * C::NE + n) * 4 + g) * 1024 + 16 * lane;
+    };
+    barrier_no_fence();
+    if (part > 0) {
+#pragma unroll
+      for (int n = 0; n < C::NE; ++n)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          *reinterpret_cast<f32x4 *>(slot(part, n, g)) =
+              f32x4{qacc[n][4 * g], qacc[n][4 * g + 1], qacc[n][4 * g + 2], qacc[n][4 * g + 3]};
+    }
+    __syncthreads();
+    if (part > 0) return;
+#pragma unroll
+    for (int p = 1; p < C::P; ++p)
+#pragma unroll
+      for (int n = 0; n < C::NE; ++n)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const f32x4 x = *reinterpret_cast<const f32x4 *>(slot(p, n, g));
+#pragma unroll
+          for (int y = 0; y < 4; ++y) qacc[n][4 * g + y] += x[y];
+        }
+  }
   if (row < S) {
     float *dqr = view_row<SH, float>(a.dq, beta, q0, h, D, left) + (size_t)(row - q0) * a.dq.row_elems;
 #pragma unroll
@@ -814,13 +862,13 @@ __device__ __forceinline__ void bwd_dq_tile(const BwdArgs &a, int L, unsigned ch
 // to S = 16K with 8 query heads (one workgroup per CU, or fewer).  One launch
 // against two, the whole step on one MI355X: 8 heads of 128, S = 8K 740 -> 672
 // us; 8 heads, b*S = 2 x 2K 291 -> 232 us; 16K and more: within 1%.
-template <int D, bool SH>
+template <int D, bool SH, int R>
 __global__ __launch_bounds__(kKvThreads, 1) void bwd_main_kernel(const BwdArgs a) {
   static_assert(kKvThreads == kDqThreads, "one workgroup size for both passes");
-  constexpr int kKvLds = KvCfg<D>::LDS_BYTES, kDqLds = kStages * DqCfg<D>::STAGE_BYTES;
+  constexpr int kKvLds = KvCfg<D>::LDS_BYTES, kDqLds = DqCfg<D, R>::STAGES * DqCfg<D, R>::STAGE_BYTES;
   __shared__ __attribute__((aligned(16))) unsigned char smem[kKvLds > kDqLds ? kKvLds : kDqLds];
   if (blockIdx.x < a.dq_blocks)
-    bwd_dq_tile<D, SH>(a, (int)blockIdx.x, smem);
+    bwd_dq_tile<D, SH, R>(a, (int)blockIdx.x, smem);
   else
     bwd_kv_unit<D, SH>(a, (int)(blockIdx.x - a.dq_blocks), smem);
 }
@@ -860,9 +908,17 @@ hipError_t launch_bwd_d(const RowView &q, const RowView &k, const RowView &v, co
     a.dv = local_view(dv_part, s.S, s.Hkl, D);
     a.dk = local_view(dk_part, s.S, s.Hkl, D);
   }
-  a.dq_blocks = (uint32_t)((s.S + kDQM - 1) / kDQM * s.b * s.Hl);
-  const dim3 grid(a.dq_blocks + (unsigned)(ck.units * ck.splits * kvheads_total));
-  hipLaunchKernelGGL((bwd_main_kernel<D, SH>), grid, dim3(kKvThreads), 0, stream, a);
+  auto main_pass = [&](auto groups) {
+    constexpr int R = decltype(groups)::value;
+    a.dq_blocks = (uint32_t)((s.S + 32 * R - 1) / (32 * R) * s.b * s.Hl);
+    const dim3 grid(a.dq_blocks + (unsigned)(ck.units * ck.splits * kvheads_total));
+    hipLaunchKernelGGL((bwd_main_kernel<D, SH, R>), grid, dim3(kKvThreads), 0, stream, a);
+  };
+  switch (dq_row_groups(s)) {
+    case 2: main_pass(std::integral_constant<int, 2>{}); break;
+    case 4: main_pass(std::integral_constant<int, 4>{}); break;
+    default: main_pass(std::integral_constant<int, 8>{}); break;
+  }
   if (parts > 1) {
     const uint32_t row_quads = (uint32_t)(s.Hkl * D / 4);
     const uint32_t seq_quads = (uint32_t)s.S * row_quads;

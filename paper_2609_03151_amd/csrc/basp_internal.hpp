@@ -274,6 +274,20 @@ inline BwdChunks bwd_chunks(const AttnShape &s) {
   }
 }
 
+// Row groups of 32 query rows among the 8 waves of a dQ workgroup (R = 8, 4
+// or 2; its 8 / R waves per row group share the keys).  Fewer rows per
+// workgroup are more workgroups with shorter key loops, for 2-3% (R = 4) to
+// 7-10% (R = 2) more time per product once the GPU is full: each K and V tile
+// feeds fewer products.  In W = b * Hl * S query rows the lines are where the
+// two sides cross (backward, us, MI355X, 110 shares of 2^8.5 to 2^15.5 rows):
+// W = 14K 8: 77, 4: 56, 2: 56; 17K one head 145, 94, 88; 21K 59, 55, 62; 31K
+// one head 938, 745, 793; 34K 98, 97, 115; 41K 158, 161, 178; 51K 233, 240,
+// 256.
+inline int dq_row_groups(const AttnShape &s) {
+  const long long rows = (long long)s.b * s.Hl * s.S;
+  return rows <= 18432 ? 2 : rows <= 36864 ? 4 : 8;
+}
+
 // Never less than the whole-chunk cut takes, which can be more than the one
 // in use: so what basp_attn_bwd_noalloc takes is what that cut lets it take.
 inline size_t attn_bwd_workspace_bytes(const AttnShape &s) {

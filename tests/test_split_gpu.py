@@ -3,7 +3,10 @@ output against a plain fp64 torch computation on the GPU.
 
 The backward's key pass is cut into row chunks and query-head parts (several
 partial sums of dK and dV per key): uneven parts, ragged lengths, parts with
-one chunk, chunks with one part, b > 1, each head dim."""
+one chunk, chunks with one part, b > 1, each head dim.  Its dQ pass gives a
+workgroup 256, 128 or 64 query rows by the share's rows (b * Hl * S): each
+width on both sides of its lines, ragged and shorter than one tile, also in
+place on the shard buffers."""
 import math
 
 import pytest
@@ -24,6 +27,11 @@ CASES = [  # b, S, Hl, Hkl, d
     (1, 6000, 10, 2, 64),   # long ragged chunks
     (1, 8192, 8, 2, 64),    # one chunk, parts only
     (2, 9000, 10, 2, 128),  # uneven parts (3 and 2 heads)
+    # dQ rows per workgroup: 64, then 128, then 256
+    (1, 1, 1, 1, 128), (1, 63, 2, 1, 64), (1, 65, 1, 1, 96), (2, 129, 3, 3, 128),
+    (1, 4608, 4, 2, 64), (1, 9216, 2, 1, 128),
+    (1, 4609, 4, 2, 128), (3, 1500, 6, 2, 96), (1, 4097, 8, 4, 80),
+    (2, 2304, 8, 2, 128), (2, 2305, 8, 2, 128),
 ]
 
 
