@@ -49,6 +49,8 @@
 //   * in the diagonal band a wave raises its issue priority over the score
 //     products, so the two waves of a SIMD drift apart: one's softmax
 //     overlaps the other's MFMAs.
+//   * small shares run attn_fwd_split_kernel, the same products with 128 or
+//     64 rows per workgroup and the keys of a tile shared among its waves.
 //   * tensors are read and written through row views: the local
 //     head-sharded tensors, or (SH) the G sequence shards of the exchange in
 //     place, whose row counts are multiples of 256 so that a workgroup's
@@ -557,12 +559,324 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
   }
 }
 
+// ---------------------------------------------------------------- split form
+// The forward of shares too small to fill the GPU with 256-row workgroups:
+// the 8 waves are R row groups of 32 query rows times P = 8 / R key parts, and
+// part p takes keys 32p .. 32p+31 of each tile of 32 P keys.  A workgroup is
+// then 32 R rows, with the same two waves per SIMD and the same products per
+// tile, for a half or a quarter of the rows and of the key loop's length.
+// Each wave runs its own online softmax over its keys; at the end parts 1 ..
+// P-1 put (reference, row sum, O) in LDS and part 0 merges them in order.  A
+// wave's tile is not software-pipelined: the loop is short.
+template <int D, int R>
+struct SplitCfg {
+  static constexpr int DC = HeadDim<D>::DC;
+  static constexpr int LW = HeadDim<D>::LW;
+  static constexpr int P = kWaves / R;
+  static constexpr int BM = 32 * R;  // query rows per workgroup
+  static constexpr int BN = 32 * P;  // keys per tile
+  static constexpr int TILE_BYTES = BN * LW * 2;
+  static constexpr int STAGES = 2 * TILE_BYTES > 32768 ? 2 : 4;  // 128 KB at 128-wide rows
+  static constexpr int LDS_BYTES = STAGES * 2 * TILE_BYTES;
+  static constexpr int NS = DC / 16;
+  static constexpr int NE = DC / 32;
+  static constexpr int CPR = LW / 8;
+  static constexpr int DMA_PER_WAVE = BN * CPR / kThreads;
+  // A part's row of the merge area: NE*4 register groups of O, the reference
+  // and the row sum, 1 KB (64 lanes x 16 B) each group, 256 B each scalar.
+  static constexpr int PART_BYTES = NE * 4 * 1024 + 512;
+  static_assert((P - 1) * R * PART_BYTES <= LDS_BYTES, "the merge area fits the ring");
+};
+
+template <int D, bool SH, int R>
+__global__ __launch_bounds__(kThreads, 1) void attn_fwd_split_kernel(
+    const RowView qv, const RowView kv, const RowView vv, const RowView ov,
+    float *__restrict__ lse, int S, int Hl, int n_rep, int heads_total, int qtiles,
+    float c /* scale * log2(e) */) {
+  using C = SplitCfg<D, R>;
+  using T = LdsTile<C::LW>;
+  // LDS: the K tiles of the ring stages, then their V tiles.
+  __shared__ __attribute__((aligned(16))) unsigned char smem[C::LDS_BYTES];
+  constexpr int kSt = C::STAGES, kVRegion = kSt * C::TILE_BYTES;
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, hh = lane >> 5;
+  const int rg = w % R, part = w / R;  // row group, key part
+
+  const int L = blockIdx.x;
+  const int qt = qtiles - 1 - L / heads_total;
+  const int hb = L % heads_total;
+  const int beta = hb / Hl, h = hb % Hl, kvh = h / n_rep;
+  const int q0 = qt * C::BM;
+  const int wrow0 = q0 + 32 * rg;
+  const int row = wrow0 + l32;
+
+  const uint32_t q_row_bytes = qv.row_elems * 2, kv_row_bytes = kv.row_elems * 2;
+  uint32_t q_left, kv_left;
+  const rsrc_t rq =
+      make_rsrc(view_row<SH, const uint16_t>(qv, beta, q0, h, D, q_left), q_left * q_row_bytes);
+  u32x4 rk = {}, rv = {};  // local: one resource per head; sharded: one per shard
+  if constexpr (!SH) {
+    rk = make_rsrc_words(view_row<false, const uint16_t>(kv, beta, 0, kvh, D, kv_left),
+                         kv_left * kv_row_bytes);
+    rv = make_rsrc_words(view_row<false, const uint16_t>(vv, beta, 0, kvh, D, kv_left),
+                         kv_left * kv_row_bytes);
+  }
+  const uint32_t smem_lds = lds_addr_of(smem);
+
+  const int kv_end = min(S, q0 + C::BM);
+  const int nt = (kv_end + C::BN - 1) / C::BN;
+  uint32_t g_off[C::DMA_PER_WAVE];
+#pragma unroll
+  for (int i = 0; i < C::DMA_PER_WAVE; ++i)
+    g_off[i] = dma_src_off<C::LW, D>((w * C::DMA_PER_WAVE + i) * 64 + lane, kv_row_bytes);
+
+  bf16x8 qf[C::NS];
+#pragma unroll
+  for (int s = 0; s < C::NS; ++s)
+    qf[s] = 2 * s < D / 8
+                ? as_bf16x8(buf_load16(rq, (uint32_t)(row - q0) * q_row_bytes + (2 * s + hh) * 16))
+                : bf16x8{};  // columns past D
+  wait_vmcnt<0>();  // retire the tracked loads before untracked copies start
+
+  uint32_t sh_tiles = 0, sh_base = 0;
+  auto load_tile = [&](int t) __attribute__((always_inline)) {
+    const uint32_t ks = smem_lds + (t % kSt) * C::TILE_BYTES;
+    uint32_t base = (uint32_t)(t * C::BN) * kv_row_bytes;
+    if constexpr (SH) {
+      if (sh_tiles == 0) {  // wave-uniform; tile t is the first of its shard
+        uint32_t left;
+        rk = make_rsrc_words(view_row<true, const uint16_t>(kv, beta, t * C::BN, kvh, D, left),
+                             left * kv_row_bytes);
+        rv = make_rsrc_words(view_row<true, const uint16_t>(vv, beta, t * C::BN, kvh, D, left),
+                             left * kv_row_bytes);
+        sh_tiles = left / C::BN;
+        sh_base = 0;
+      }
+      base = sh_base;
+      sh_base += C::BN * kv_row_bytes;
+      --sh_tiles;
+    }
+#pragma unroll
+    for (int i = 0; i < C::DMA_PER_WAVE; ++i) {
+      const uint32_t lds_off = ks + (w * C::DMA_PER_WAVE + i) * 1024;
+      buf_load16_lds_async(rk, base + g_off[i], lds_off);
+      buf_load16_lds_async(rv, base + g_off[i], lds_off + kVRegion);
+    }
+  };
+  // Tiles 0 .. kSt-2 are issued up front; iteration t waits for its own copies
+  // of tile t, passes the barrier and issues tile t + kSt-1 into the stage of
+  // tile t-1, which every wave has finished with.
+  auto begin_tile = [&](int t) __attribute__((always_inline)) {
+    if constexpr (kSt == 4) {
+      const int ahead = min(2, nt - 1 - t);
+      if (ahead >= 2) wait_vmcnt<4 * C::DMA_PER_WAVE>();
+      else if (ahead == 1) wait_vmcnt<2 * C::DMA_PER_WAVE>();
+      else wait_vmcnt<0>();
+    } else {
+      wait_vmcnt<0>();
+    }
+    barrier_no_fence();
+    if (t + kSt - 1 < nt) load_tile(t + kSt - 1);
+  };
+#pragma unroll
+  for (int t = 0; t < kSt - 1; ++t)
+    if (t < nt) load_tile(t);
+
+  // This lane's operand reads: K row l32 and V^T rows of the wave's part.
+  const int part_off = part * 32 * T::ROW_BYTES;
+  int k_off[C::NS], v_off[C::NE][2];
+#pragma unroll
+  for (int s = 0; s < C::NS; ++s) {
+    k_off[s] = T::off(l32, 2 * s + hh) + part_off;
+    asm volatile("" : "+v"(k_off[s]));
+  }
+#pragma unroll
+  for (int n = 0; n < C::NE; ++n)
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      v_off[n][x] = kVRegion + part_off +
+                    tr_piece_off<C::LW>(4 * hh + 8 * x, 32 * n + 16 * ((lane >> 4) & 1), lane);
+      asm volatile("" : "+v"(v_off[n][x]));
+    }
+
+  f32x16 oacc[C::NE];
+#pragma unroll
+  for (int n = 0; n < C::NE; ++n)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) oacc[n][r] = 0.f;
+  float m_ref = -INFINITY, l_run = 0.f;  // -inf: no key of this part reached the row yet
+
+  auto tile = [&](int t, int st, auto mask_tag) __attribute__((always_inline)) {
+    constexpr bool MASK = decltype(mask_tag)::value;
+    const int j0 = t * C::BN + 32 * part;
+    if (MASK && j0 > wrow0 + 31) return;  // wave-uniform: every key past every row
+    const unsigned char *Ks = smem + st * C::TILE_BYTES;
+    wave_priority<1>();
+    f32x16 sacc;
+#pragma unroll
+    for (int s = 0; s < C::NS; ++s) {
+      const bf16x8 a = *reinterpret_cast<const bf16x8 *>(Ks + k_off[s]);
+      sacc = mfma32x32x16(a, qf[s], s == 0 ? f32x16{} : sacc);
+    }
+    wave_priority<0>();
+    // sacc[r] = S^T[key j0 + 8(r/4) + 4hh + r%4][query row]
+    if constexpr (MASK) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (j0 + 8 * (r >> 2) + 4 * hh + (r & 3) > row) sacc[r] = -INFINITY;
+    }
+    float mx = -INFINITY;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[r]);
+    mx = pair_max(mx) * c;
+    const bool grow = mx > m_ref + kRescaleSlack;
+    if (__builtin_amdgcn_ballot_w64(grow)) {  // wave-uniform, rare after the first tiles
+      asm volatile("" ::: "memory");
+      const float alpha = grow ? fast_exp2(m_ref - mx) : 1.f;
+      m_ref = grow ? mx : m_ref;
+      l_run *= alpha;
+#pragma unroll
+      for (int n = 0; n < C::NE; ++n)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) oacc[n][r] *= alpha;
+    }
+    // A row no key of the part has reached: every score is -inf, P = 0.
+    const float m_use = m_ref == -INFINITY ? 0.f : m_ref;
+    float psum = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      sacc[r] = fast_exp2(fmaf(sacc[r], c, -m_use));
+      psum += sacc[r];
+    }
+    l_run += psum;
+    bf16x8 pf[2];
+#pragma unroll
+    for (int s2 = 0; s2 < 2; ++s2) {
+      const int b8 = 8 * s2;
+      pf[s2] = as_bf16x8(u32x4{pack_bf16x2(sacc[b8 + 0], sacc[b8 + 1]),
+                               pack_bf16x2(sacc[b8 + 2], sacc[b8 + 3]),
+                               pack_bf16x2(sacc[b8 + 4], sacc[b8 + 5]),
+                               pack_bf16x2(sacc[b8 + 6], sacc[b8 + 7])});
+    }
+#pragma unroll
+    for (int n = 0; n < C::NE; ++n)
+#pragma unroll
+      for (int s2 = 0; s2 < 2; ++s2) {
+        const bf16x8 a = tr_operand(Ks, v_off[n][0] + s2 * 16 * T::ROW_BYTES,
+                                    v_off[n][1] + s2 * 16 * T::ROW_BYTES);
+        oacc[n] = mfma32x32x16(a, pf[s2], oacc[n]);
+      }
+    __builtin_amdgcn_sched_group_barrier(kSchedDsRead, 4, 0);
+#pragma unroll
+    for (int i = 0; i < 2 * C::NE - 2; ++i) {
+      __builtin_amdgcn_sched_group_barrier(kSchedMfma, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(kSchedDsRead, 2, 0);
+    }
+    __builtin_amdgcn_sched_group_barrier(kSchedMfma, 2, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  const int t_mask = min(nt, q0 / C::BN);  // tiles before t_mask need no mask
+  int t = 0;
+  for (; t + kSt <= t_mask; t += kSt) {  // t % kSt == 0: constant stage offsets
+#pragma unroll
+    for (int u = 0; u < kSt; ++u) {
+      begin_tile(t + u);
+      tile(t + u, u, std::false_type{});
+    }
+  }
+  for (; t < t_mask; ++t) {
+    begin_tile(t);
+    tile(t, t % kSt, std::false_type{});
+  }
+  for (; t < nt; ++t) {
+    begin_tile(t);
+    tile(t, t % kSt, std::true_type{});
+  }
+
+  // Merge (every copy landed, nothing left to read in the ring).
+  float l_tot = pair_sum(l_run);
+  auto area = [&](int p) __attribute__((always_inline)) {
+    return smem + ((p - 1) * R + rg) * C::PART_BYTES;
+  };
+  barrier_no_fence();
+  if (part > 0) {
+    unsigned char *a = area(part);
+#pragma unroll
+    for (int n = 0; n < C::NE; ++n)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        *reinterpret_cast<f32x4 *>(a + (n * 4 + g) * 1024 + 16 * lane) =
+            f32x4{oacc[n][4 * g], oacc[n][4 * g + 1], oacc[n][4 * g + 2], oacc[n][4 * g + 3]};
+    *reinterpret_cast<float *>(a + C::NE * 4096 + 4 * lane) = m_ref;
+    *reinterpret_cast<float *>(a + C::NE * 4096 + 256 + 4 * lane) = l_tot;
+  }
+  __syncthreads();
+  if (part > 0 || row >= S) return;
+  float m_all = m_ref;
+  float pm[C::P], wt[C::P];
+  pm[0] = m_ref;
+#pragma unroll
+  for (int p = 1; p < C::P; ++p) {
+    pm[p] = *reinterpret_cast<const float *>(area(p) + C::NE * 4096 + 4 * lane);
+    m_all = fmaxf(m_all, pm[p]);
+  }
+#pragma unroll
+  for (int p = 0; p < C::P; ++p) wt[p] = pm[p] == -INFINITY ? 0.f : fast_exp2(pm[p] - m_all);
+  l_tot *= wt[0];
+#pragma unroll
+  for (int p = 1; p < C::P; ++p)
+    l_tot = fmaf(wt[p], *reinterpret_cast<const float *>(area(p) + C::NE * 4096 + 256 + 4 * lane),
+                 l_tot);
+  const float inv = 1.f / l_tot;
+  uint32_t o_left;
+  uint16_t *ob = view_row<SH, uint16_t>(ov, beta, q0, h, D, o_left) +
+                 (size_t)(row - q0) * ov.row_elems;
+#pragma unroll
+  for (int n = 0; n < C::NE; ++n)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      if (32 * n + 8 * g >= D) continue;  // padding columns
+      f32x4 x;
+#pragma unroll
+      for (int y = 0; y < 4; ++y) x[y] = oacc[n][4 * g + y] * wt[0];
+#pragma unroll
+      for (int p = 1; p < C::P; ++p) {
+        const f32x4 z =
+            *reinterpret_cast<const f32x4 *>(area(p) + (n * 4 + g) * 1024 + 16 * lane);
+#pragma unroll
+        for (int y = 0; y < 4; ++y) x[y] = fmaf(wt[p], z[y], x[y]);
+      }
+      *reinterpret_cast<u32x2 *>(ob + 32 * n + 8 * g + 4 * hh) =
+          u32x2{pack_bf16x2(x[0] * inv, x[1] * inv), pack_bf16x2(x[2] * inv, x[3] * inv)};
+    }
+  if (hh == 0)
+    lse[((size_t)beta * Hl + h) * S + row] = (m_all + fast_log2(l_tot)) * 0.69314718055994531f;
+}
+
+// Row groups of a workgroup: 8 (attn_fwd_kernel), 4 or 2.  Up to the lines
+// below (in W = b * Hl * S query rows) the 256-row workgroups, causal and so
+// of very different lengths, leave CUs idle; past them the pipelined kernel's
+// higher rate wins.  At d = 64 two split workgroups fit a CU, so the line
+// lies higher.  Forward, us on MI355X, R = 8, 4, 2 (110 shares of 256 to 45K
+// rows): d = 128: W = 4.4K 18, 15, 11; 16K 45, 32, 22; 36K 37, 28, 33; 50K
+// 123, 96, 103; 66K (8 heads, S = 8K) 186, 125, -; 76K 215, 207, 226; 86K 137,
+// 141, 156; 110K 356, 401, 433.  d = 64: 28K 53, 37, 26; 45K 85, 60, 58; 79K 55,
+// 48, 64; 113K 331, 319, 394; 131K 290, 301, -.
+int row_groups(const AttnShape &s) {
+  const long long rows = (long long)s.b * s.Hl * s.S;
+  if (rows <= 35840) return 2;
+  return rows <= (s.d == 64 ? 122880 : 73728) ? 4 : 8;
+}
+
 }  // namespace
 
 hipError_t launch_attn_fwd(const RowView &q, const RowView &k, const RowView &v,
                            const RowView &o, float *lse, const AttnShape &s, bool sharded,
                            hipStream_t stream) {
-  const int qtiles = (s.S + kBM - 1) / kBM;
+  const int R = row_groups(s);
+  const int qtiles = (s.S + 32 * R - 1) / (32 * R);
   const int heads_total = s.b * s.Hl;
   const long long blocks = (long long)qtiles * heads_total;
   if (blocks == 0) return hipSuccess;
@@ -572,13 +886,21 @@ hipError_t launch_attn_fwd(const RowView &q, const RowView &k, const RowView &v,
     hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kThreads), 0, stream, q, k, v, o, lse,
                        s.S, s.Hl, n_rep, heads_total, qtiles, c);
   };
-  auto by_dim = [&](auto sh) {
+  auto by_groups = [&](auto dim, auto sh) {
+    constexpr int D = decltype(dim)::value;
     constexpr bool SH = decltype(sh)::value;
+    switch (R) {
+      case 2: go(attn_fwd_split_kernel<D, SH, 2>); break;
+      case 4: go(attn_fwd_split_kernel<D, SH, 4>); break;
+      default: go(attn_fwd_kernel<D, SH>); break;
+    }
+  };
+  auto by_dim = [&](auto sh) {
     switch (s.d) {
-      case 64: go(attn_fwd_kernel<64, SH>); break;
-      case 80: go(attn_fwd_kernel<80, SH>); break;
-      case 96: go(attn_fwd_kernel<96, SH>); break;
-      default: go(attn_fwd_kernel<128, SH>); break;
+      case 64: by_groups(std::integral_constant<int, 64>{}, sh); break;
+      case 80: by_groups(std::integral_constant<int, 80>{}, sh); break;
+      case 96: by_groups(std::integral_constant<int, 96>{}, sh); break;
+      default: by_groups(std::integral_constant<int, 128>{}, sh); break;
     }
   };
   if (sharded)

@@ -5,8 +5,11 @@ The backward's key pass is cut into row chunks and query-head parts (several
 partial sums of dK and dV per key): uneven parts, ragged lengths, parts with
 one chunk, chunks with one part, b > 1, each head dim.  Its dQ pass gives a
 workgroup 256, 128 or 64 query rows by the share's rows (b * Hl * S): each
-width on both sides of its lines, ragged and shorter than one tile, also in
-place on the shard buffers."""
+width on both sides of its lines, ragged and shorter than one tile.  The
+forward gives a workgroup 256, 128 or 64 query rows likewise; its split kernels
+are also run on scores that grow along the sequence (the reference of every
+key part moves, parts of very different weight), on rows most key parts never
+reach, and in place on the shard buffers."""
 import math
 
 import pytest
@@ -32,6 +35,9 @@ CASES = [  # b, S, Hl, Hkl, d
     (1, 4608, 4, 2, 64), (1, 9216, 2, 1, 128),
     (1, 4609, 4, 2, 128), (3, 1500, 6, 2, 96), (1, 4097, 8, 4, 80),
     (2, 2304, 8, 2, 128), (2, 2305, 8, 2, 128),
+    # forward rows per workgroup: 64 | 128 and 128 | 256
+    (1, 4480, 8, 2, 128), (1, 4481, 8, 2, 96), (1, 9216, 8, 2, 80), (1, 9217, 8, 2, 80),
+    (3, 5120, 8, 4, 64), (3, 5121, 8, 4, 64),
 ]
 
 
@@ -81,3 +87,45 @@ def test_split_attention_matches_fp64(b, S, Hl, Hkl, d):
     for name, got, want in zip(("O", "LSE", "dQ", "dK", "dV"), (o, lse, dq, dk, dv), ref):
         bar = dict(max_abs=LSE_MAX_ABS, mean_abs=LSE_MAX_ABS) if name == "LSE" else {}
         check_close(name, f(got), f(want), **bar)
+
+
+@pytest.mark.parametrize("b,S,Hl,Hkl,d", [
+    (1, 1000, 4, 1, 128), (2, 700, 2, 2, 64),   # 64 rows per workgroup
+    (1, 5000, 8, 1, 128), (1, 5000, 8, 1, 80),  # 128
+])
+@pytest.mark.parametrize("peak", ["late", "early"])
+def test_split_forward_parts_of_unlike_weight(b, S, Hl, Hkl, d, peak):
+    """Scores that rise (or fall) along the keys by tens of units: each key
+    part's running reference moves many times, and a row's parts differ in
+    weight by many orders of magnitude when they are merged."""
+    log(f"[split ramp] b={b} S={S} Hl={Hl} Hkl={Hkl} d={d} {peak}")
+    g = torch.Generator("cuda").manual_seed(S + d)
+    mk = lambda n: torch.randn((b, S, n, d), generator=g, device="cuda")
+    q, k, v, do = mk(Hl), mk(Hkl), mk(Hkl), mk(Hl)
+    ramp = torch.linspace(0, 40, S, device="cuda")[None, :, None]
+    q[..., 0], k[..., 0] = d ** 0.25, (ramp if peak == "late" else -ramp) * d ** 0.25
+    q, k, v, do = (t.to(torch.bfloat16) for t in (q, k, v, do))
+    o, lse = basp.attn_fwd(q, k, v)
+    ref = _reference(q, k, v, do, d ** -0.5)
+    f = lambda t: t.double().cpu().numpy()
+    check_close("O", f(o), f(ref[0]))
+    check_close("LSE", f(lse), f(ref[1]), max_abs=LSE_MAX_ABS, mean_abs=LSE_MAX_ABS)
+
+
+@pytest.mark.parametrize("S", [1024, 5120, 16384])
+@pytest.mark.parametrize("d", [64, 128])
+def test_split_forward_in_place(S, d):
+    """The three workgroup widths read the shards as they read local tensors."""
+    G, b, n, rank = 2, 1, 8, 1
+    g = torch.Generator("cuda").manual_seed(S + d)
+    mk = lambda h: [torch.randn((b, S // G, h, d), generator=g, device="cuda").to(torch.bfloat16)
+                    for _ in range(G)]
+    q, k, v = mk(2 * n), mk(2), mk(2)
+    o_sh = [torch.zeros_like(t) for t in q]
+    lse_sh = basp.attn_fwd_sharded(q, k, v, o_sh, rank)
+    local = basp.pack_qkv(q, k, v, rank)
+    o, lse = basp.attn_fwd(*local, G=G)
+    torch.cuda.synchronize()
+    got = torch.cat([t[:, :, rank * n:(rank + 1) * n] for t in o_sh], dim=1)
+    assert torch.equal(got.view(torch.int16), o.view(torch.int16))
+    assert torch.equal(lse_sh, lse)
