@@ -98,18 +98,37 @@ def _check(rc: int, what: str):
         raise BaspError(rc, what)
 
 
-def _stream(t: torch.Tensor):
-    return ctypes.c_void_p(torch.cuda.current_stream(t.device).cuda_stream)
+# A small share's calls take about as long on the host as on the GPU, so the
+# marshalling below avoids temporary objects: raw integers for pointers and for
+# the stream (torch's raw stream handle, 0.1 us, instead of a Stream object, 2
+# us), one array type per table length.
+def _stream(t: torch.Tensor) -> int:
+    return torch._C._cuda_getCurrentRawStream(t.get_device())
 
 
-def _dev(t: torch.Tensor, name: str, dtype=None):
+def _dev(t: torch.Tensor, name: str, dtype=None) -> int:
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise TypeError(f"{name} must be a CUDA (HIP) tensor")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
     if dtype is not None and t.dtype != dtype:
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+_table_types: dict = {}
+
+
+def _table(tensors, name: str, dtype, n: int):
+    """Pointer table of n device tensors, each checked as _dev does (missing ones are NULL)."""
+    kind = _table_types.get(n)
+    if kind is None:
+        kind = _table_types[n] = ctypes.c_void_p * n
+    for t in tensors:
+        if not (isinstance(t, torch.Tensor) and t.is_cuda and t.is_contiguous()
+                and t.dtype == dtype):  # _dev says which tensor, and why
+            return kind(*[_dev(t, f"{name}[{j}]", dtype) for j, t in enumerate(tensors)])
+    return kind(*[t.data_ptr() for t in tensors])
 
 
 def _dtype_code(t: torch.Tensor) -> int:
@@ -147,10 +166,10 @@ def pack(shards, rank: int, out: torch.Tensor | None = None) -> torch.Tensor:
     """G shards [b, S/G, n, d] -> the rank's head-sharded [b, S, nl, d]."""
     G = len(shards)
     b, Sg, n, d = shards[0].shape
-    ptrs = (ctypes.c_void_p * G)(*[_dev(s, f"shards[{j}]", shards[0].dtype).value
-                                   for j, s in enumerate(shards)])
+    ptrs = _table(shards, "shards", shards[0].dtype, G)
+    shape, device = shards[0].shape, shards[0].device
     for s in shards:
-        if s.shape != shards[0].shape or s.device != shards[0].device:
+        if s.shape != shape or s.device != device:
             raise ValueError("shards differ in shape or device")
     if out is None:
         out = torch.empty((b, Sg * G, heads_per_member(n, G), d), dtype=shards[0].dtype,
@@ -164,8 +183,7 @@ def unpack(local: torch.Tensor, shards, rank: int):
     """Write local [b, S, n/G, d] into the rank's head slice of every shard."""
     G = len(shards)
     b, Sg, n, d = shards[0].shape
-    ptrs = (ctypes.c_void_p * G)(*[_dev(s, f"shards[{j}]", local.dtype).value
-                                   for j, s in enumerate(shards)])
+    ptrs = _table(shards, "shards", local.dtype, G)
     _check(lib().basp_unpack(_dev(local, "local"), ptrs, b, Sg * G, n, d, G, rank,
                              _dtype_code(local), _stream(local)), "basp_unpack")
     return shards
@@ -176,8 +194,7 @@ def unpack_add(local: torch.Tensor, shards, rank: int):
     (gradients of kv heads that several members share)."""
     G = len(shards)
     b, Sg, n, d = shards[0].shape
-    ptrs = (ctypes.c_void_p * G)(*[_dev(s, f"shards[{j}]", torch.float32).value
-                                   for j, s in enumerate(shards)])
+    ptrs = _table(shards, "shards", torch.float32, G)
     _check(lib().basp_unpack_add(_dev(local, "local", torch.float32), ptrs, b, Sg * G, n, d, G,
                                  rank, _stream(local)), "basp_unpack_add")
     return shards
@@ -196,10 +213,10 @@ def pack_qkv(q_shards, k_shards, v_shards, rank: int, q=None, k=None, v=None):
         k = torch.empty((b, Sg * G, heads_per_member(H_kv, G), d), dtype=dt, device=dev)
     if v is None:
         v = torch.empty_like(k)
-    tab = lambda xs, nm: (ctypes.c_void_p * G)(*[_dev(t, f"{nm}[{j}]", dt).value
-                                                 for j, t in enumerate(xs)])
-    _check(lib().basp_pack_qkv(tab(q_shards, "q_shards"), tab(k_shards, "k_shards"),
-                               tab(v_shards, "v_shards"), _dev(q, "q", dt), _dev(k, "k", dt),
+    _check(lib().basp_pack_qkv(_table(q_shards, "q_shards", dt, G),
+                               _table(k_shards, "k_shards", dt, G),
+                               _table(v_shards, "v_shards", dt, G), _dev(q, "q", dt),
+                               _dev(k, "k", dt),
                                _dev(v, "v", dt), b, Sg * G, H, H_kv, d, G, rank, _dtype_code(q),
                                _stream(q)), "basp_pack_qkv")
     return q, k, v
@@ -212,12 +229,11 @@ def unpack_grads(dq, dk, dv, dq_shards, dk_shards, dv_shards, rank: int):
     b, Sg, H, d = dq_shards[0].shape
     H_kv = dk_shards[0].shape[2]
     f32 = torch.float32
-    tab = lambda xs, nm: (ctypes.c_void_p * G)(*[_dev(t, f"{nm}[{j}]", f32).value
-                                                 for j, t in enumerate(xs)])
     _check(lib().basp_unpack_grads(_dev(dq, "dq", f32), _dev(dk, "dk", f32), _dev(dv, "dv", f32),
-                                   tab(dq_shards, "dq_shards"), tab(dk_shards, "dk_shards"),
-                                   tab(dv_shards, "dv_shards"), b, Sg * G, H, H_kv, d, G, rank,
-                                   _stream(dq)), "basp_unpack_grads")
+                                   _table(dq_shards, "dq_shards", f32, G),
+                                   _table(dk_shards, "dk_shards", f32, G),
+                                   _table(dv_shards, "dv_shards", f32, G), b, Sg * G, H, H_kv, d,
+                                   G, rank, _stream(dq)), "basp_unpack_grads")
 
 
 def a2a_pack(own: torch.Tensor, G: int, out: torch.Tensor | None = None) -> torch.Tensor:
@@ -314,8 +330,8 @@ def attn_bwd(q, k, v, o, lse, do, G: int = 1, scale: float | None = None,
         dk = torch.empty(k.shape, dtype=torch.float32, device=q.device)
     if dv is None:
         dv = torch.empty(v.shape, dtype=torch.float32, device=q.device)
-    need = attn_bwd_workspace_bytes(b, S, H, H_kv, d, G)
     if workspace is None:
+        need = attn_bwd_workspace_bytes(b, S, H, H_kv, d, G)
         workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=q.device)
     _check(lib().basp_attn_bwd(
         _dev(q, "q", torch.bfloat16), _dev(k, "k", torch.bfloat16),
@@ -345,9 +361,8 @@ def attn_bwd_noalloc(q, k, v, o, lse, do, dq, dk, dv, G: int = 1, scale: float |
 
 
 # ------------------------------------------------- attention on the shards
-def _table(shards, name, dtype):
-    return (ctypes.c_void_p * len(shards))(*[_dev(t, f"{name}[{j}]", dtype).value
-                                             for j, t in enumerate(shards)])
+def _shards(shards, name: str, dtype, G: int):
+    return _table(shards, name, dtype, max(G, len(shards)))
 
 
 def attn_fwd_sharded(q_shards, k_shards, v_shards, o_shards, rank: int,
@@ -364,8 +379,8 @@ def attn_fwd_sharded(q_shards, k_shards, v_shards, o_shards, rank: int,
         lse = torch.empty((b, H // G, S), dtype=torch.float32, device=q_shards[0].device)
     bf = torch.bfloat16
     _check(lib().basp_attn_fwd_sharded(
-        _table(q_shards, "q", bf), _table(k_shards, "k", bf), _table(v_shards, "v", bf),
-        _table(o_shards, "o", bf), _dev(lse, "lse", torch.float32), b, S, H, H_kv, d, G, rank,
+        _shards(q_shards, "q", bf, G), _shards(k_shards, "k", bf, G), _shards(v_shards, "v", bf, G),
+        _shards(o_shards, "o", bf, G), _dev(lse, "lse", torch.float32), b, S, H, H_kv, d, G, rank,
         float(scale), _stream(lse)), "basp_attn_fwd_sharded")
     return lse
 
@@ -382,13 +397,14 @@ def attn_bwd_sharded(q_shards, k_shards, v_shards, o_shards, lse, do_shards, dq_
     H_kv = k_shards[0].shape[2]
     S = Sg * G
     scale = d ** -0.5 if scale is None else scale
-    need = attn_bwd_sharded_workspace_bytes(b, S, H, H_kv, d, G)
     if workspace is None:
+        need = attn_bwd_sharded_workspace_bytes(b, S, H, H_kv, d, G)
         workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=lse.device)
     bf, f32 = torch.bfloat16, torch.float32
     _check(lib().basp_attn_bwd_sharded(
-        _table(q_shards, "q", bf), _table(k_shards, "k", bf), _table(v_shards, "v", bf),
-        _table(o_shards, "o", bf), _dev(lse, "lse", f32), _table(do_shards, "do", bf),
-        _table(dq_shards, "dq", f32), _table(dk_shards, "dk", f32), _table(dv_shards, "dv", f32),
+        _shards(q_shards, "q", bf, G), _shards(k_shards, "k", bf, G), _shards(v_shards, "v", bf, G),
+        _shards(o_shards, "o", bf, G), _dev(lse, "lse", f32), _shards(do_shards, "do", bf, G),
+        _shards(dq_shards, "dq", f32, G), _shards(dk_shards, "dk", f32, G),
+        _shards(dv_shards, "dv", f32, G),
         _dev(workspace, "workspace"), workspace.numel() * workspace.element_size(),
         b, S, H, H_kv, d, G, rank, float(scale), _stream(lse)), "basp_attn_bwd_sharded")
