@@ -174,7 +174,7 @@ struct KvCfg {
   static constexpr int TILE_BYTES = kQM * LW * 2;   // a step's Q or dO rows
   static constexpr int KT_BYTES = kKN * LW * 2;     // the workgroup's V rows
   static constexpr int AUX_BYTES = 1024;            // LSE2, then -D, of the step's rows
-  static constexpr int NS = DC / 16;
+  static constexpr int NS = D / 16;
   static constexpr int NE = DC / 32;
   static constexpr int CPR = LW / 8;
   static constexpr int DMA_PER_WAVE = kQM * CPR / kKvThreads;     // 1 KB copies per tile
@@ -239,7 +239,7 @@ __device__ __forceinline__ void bwd_kv_unit(const BwdArgs &a, int L, unsigned ch
 #pragma unroll
     for (int s = 0; s < C::NS; ++s) {
       const uint32_t off = (uint32_t)(key - k0) * kv_row_bytes + (2 * s + hh) * 16;
-      kf[s] = 2 * s < D / 8 ? as_bf16x8(buf_load16(rk, off)) : bf16x8{};  // columns past D
+      kf[s] = as_bf16x8(buf_load16(rk, off));
     }
     if constexpr (kVRegs) {
       const rsrc_t rv = make_rsrc(local_row(vv, beta, k0, kvh, D, left),
@@ -247,7 +247,7 @@ __device__ __forceinline__ void bwd_kv_unit(const BwdArgs &a, int L, unsigned ch
 #pragma unroll
       for (int s = 0; s < C::NS; ++s) {
         const uint32_t off = (uint32_t)(key - k0) * kv_row_bytes + (2 * s + hh) * 16;
-        vf[s] = 2 * s < D / 8 ? as_bf16x8(buf_load16(rv, off)) : bf16x8{};
+        vf[s] = as_bf16x8(buf_load16(rv, off));
       }
     }
     wait_vmcnt<0>();  // retire the tracked loads before untracked copies start
@@ -589,7 +589,7 @@ struct DqCfg {
   static constexpr int TILE_BYTES = BN * LW * 2;
   static constexpr int STAGE_BYTES = 2 * TILE_BYTES;  // K, V
   static constexpr int STAGES = STAGE_BYTES > 32768 ? 2 : 4;
-  static constexpr int NS = DC / 16;
+  static constexpr int NS = D / 16;
   static constexpr int NE = DC / 32;
   static constexpr int CPR = LW / 8;
   static constexpr int DMA_PER_WAVE = BN * CPR / kDqThreads;
@@ -639,13 +639,8 @@ __device__ __forceinline__ void bwd_dq_tile(const BwdArgs &a, int L, unsigned ch
   bf16x8 qf[C::NS], df[C::NS];
 #pragma unroll
   for (int s = 0; s < C::NS; ++s) {
-    if (2 * s < D / 8) {
-      qf[s] = as_bf16x8(buf_load16(rq, (uint32_t)(row - q0) * q_row_bytes + (2 * s + hh) * 16));
-      df[s] = as_bf16x8(buf_load16(rd, (uint32_t)(row - q0) * q_row_bytes + (2 * s + hh) * 16));
-    } else {  // columns past D
-      qf[s] = bf16x8{};
-      df[s] = bf16x8{};
-    }
+    qf[s] = as_bf16x8(buf_load16(rq, (uint32_t)(row - q0) * q_row_bytes + (2 * s + hh) * 16));
+    df[s] = as_bf16x8(buf_load16(rd, (uint32_t)(row - q0) * q_row_bytes + (2 * s + hh) * 16));
   }
   float lse2 = INFINITY, nd = 0.f;  // rows past S: P = 0
   if (row < S) {

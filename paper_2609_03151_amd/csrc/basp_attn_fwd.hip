@@ -80,11 +80,11 @@ constexpr int kSchedDsRead = 0x100;
 
 template <int D>
 struct FwdCfg {
-  static constexpr int DC = HeadDim<D>::DC;  // computed width (columns past D are zero)
+  static constexpr int DC = HeadDim<D>::DC;  // computed width of O
   static constexpr int LW = HeadDim<D>::LW;  // LDS row layout
   static constexpr int TILE_BYTES = kBN * LW * 2;
   static constexpr int STAGE_BYTES = 2 * TILE_BYTES;  // K, V
-  static constexpr int NS = DC / 16;                  // 16-deep steps over the head dim
+  static constexpr int NS = D / 16;                   // 16-deep steps over the head dim
   static constexpr int NE = DC / 32;                  // 32-wide head-dim subtiles of O
   static constexpr int CPR = LW / 8;                  // 16-byte chunk slots per LDS row
   static constexpr int DMA_PER_WAVE = kBN * CPR / kThreads;  // 1 KB loads per wave per tensor
@@ -133,9 +133,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
   bf16x8 qf[C::NS];
 #pragma unroll
   for (int s = 0; s < C::NS; ++s)
-    qf[s] = 2 * s < D / 8
-                ? as_bf16x8(buf_load16(rq, (uint32_t)(row - q0) * q_row_bytes + (2 * s + hh) * 16))
-                : bf16x8{};  // columns past D
+    qf[s] = as_bf16x8(buf_load16(rq, (uint32_t)(row - q0) * q_row_bytes + (2 * s + hh) * 16));
   // Retire the Q loads before any tile copy is in flight: the compiler does
   // not count the copies, and a wait for Q inside the tile loop would also
   // drain the prefetched tiles.
@@ -578,7 +576,7 @@ struct SplitCfg {
   static constexpr int TILE_BYTES = BN * LW * 2;
   static constexpr int STAGES = 2 * TILE_BYTES > 32768 ? 2 : 4;  // 128 KB at 128-wide rows
   static constexpr int LDS_BYTES = STAGES * 2 * TILE_BYTES;
-  static constexpr int NS = DC / 16;
+  static constexpr int NS = D / 16;
   static constexpr int NE = DC / 32;
   static constexpr int CPR = LW / 8;
   static constexpr int DMA_PER_WAVE = BN * CPR / kThreads;
@@ -635,9 +633,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_split_kernel(
   bf16x8 qf[C::NS];
 #pragma unroll
   for (int s = 0; s < C::NS; ++s)
-    qf[s] = 2 * s < D / 8
-                ? as_bf16x8(buf_load16(rq, (uint32_t)(row - q0) * q_row_bytes + (2 * s + hh) * 16))
-                : bf16x8{};  // columns past D
+    qf[s] = as_bf16x8(buf_load16(rq, (uint32_t)(row - q0) * q_row_bytes + (2 * s + hh) * 16));
   wait_vmcnt<0>();  // retire the tracked loads before untracked copies start
 
   uint32_t sh_tiles = 0, sh_base = 0;

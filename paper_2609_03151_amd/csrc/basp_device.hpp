@@ -179,10 +179,13 @@ struct LdsTile<64> {
   }
 };
 
-// Head dims the attention kernels take, with the width their MFMA tiles
-// compute at (DC, a multiple of 32) and the LDS row layout they use (LW):
-// 80 and 96 compute at 96, kept in the 128-wide layout; the columns past D
-// are zeros everywhere they enter a product.
+// Head dims the attention kernels take, with the width their outputs are
+// computed at (DC, a multiple of the 32-wide accumulator tile) and the LDS row
+// layout they use (LW): 80 and 96 compute outputs of 96, kept in the 128-wide
+// layout, and the columns past D are not stored.  Contractions over the head
+// dim take D / 16 steps: 80 is five of them, six when padded like the outputs
+// (the d = 80 layer, forward and backward, of 16K tokens, 8 heads on 2: 1513
+// us with six, 1459 with five).
 template <int D>
 struct HeadDim;
 template <>
