@@ -49,8 +49,8 @@
 //   * in the diagonal band a wave raises its issue priority over the score
 //     products, so the two waves of a SIMD drift apart: one's softmax
 //     overlaps the other's MFMAs.
-//   * small shares run attn_fwd_split_kernel, the same products with 128 or
-//     64 rows per workgroup and the keys of a tile shared among its waves.
+//   * small shares run 128- or 64-row workgroups whose waves share the keys of
+//     a tile (P = 2 below, and attn_fwd_split_kernel).
 //   * tensors are read and written through row views: the local
 //     head-sharded tensors, or (SH) the G sequence shards of the exchange in
 //     place, whose row counts are multiples of 256 so that a workgroup's
@@ -68,34 +68,103 @@ namespace {
 
 constexpr int kThreads = 512;
 constexpr int kWaves = 8;
-constexpr int kBM = 32 * kWaves;   // query rows per workgroup
-constexpr int kStages = 4;
-constexpr int kPD = 2;            // tiles in flight behind the one being read
-constexpr int kBN = 64;           // keys per tile
+constexpr int kBN = 64;           // keys per wave and tile
 constexpr float kRescaleSlack = 8.f;  // log2 headroom before the reference max moves
 // Instruction classes of __builtin_amdgcn_sched_group_barrier.
 constexpr int kSchedValu = 0x002;
 constexpr int kSchedMfma = 0x008;
 constexpr int kSchedDsRead = 0x100;
 
-template <int D>
+// P = 1: the 8 waves are 8 row groups of 32 query rows, which share every tile
+// of 64 keys.  P = 2 (small shares): 4 row groups, and two waves of a row group
+// take the two halves of a tile of 128 keys, each with its own online softmax,
+// merged once through LDS.
+template <int D, int PARTS>
 struct FwdCfg {
+  static constexpr int P = PARTS;
   static constexpr int DC = HeadDim<D>::DC;  // computed width of O
   static constexpr int LW = HeadDim<D>::LW;  // LDS row layout
-  static constexpr int TILE_BYTES = kBN * LW * 2;
+  static constexpr int R = kWaves / P;            // row groups
+  static constexpr int BM = 32 * R;               // query rows per workgroup
+  static constexpr int BT = kBN * P;              // keys per tile
+  static constexpr int STAGES = P == 1 ? 4 : 2;
+  static constexpr int PD = 2;                    // P = 1: tiles in flight behind the one being read
+  static constexpr int TILE_BYTES = BT * LW * 2;
   static constexpr int STAGE_BYTES = 2 * TILE_BYTES;  // K, V
   static constexpr int NS = D / 16;                   // 16-deep steps over the head dim
   static constexpr int NE = DC / 32;                  // 32-wide head-dim subtiles of O
   static constexpr int CPR = LW / 8;                  // 16-byte chunk slots per LDS row
-  static constexpr int DMA_PER_WAVE = kBN * CPR / kThreads;  // 1 KB loads per wave per tensor
+  static constexpr int DMA_PER_WAVE = BT * CPR / kThreads;  // 1 KB loads per wave per tensor
+  // A part's slot of the merge area: NE*4 register groups of O (1 KB each: 64
+  // lanes x 16 B), then the reference and the row sum (256 B each).
+  static constexpr int PART_BYTES = NE * 4 * 1024 + 512;
+  static_assert((P - 1) * R * PART_BYTES <= STAGES * STAGE_BYTES, "the merge area fits the ring");
 };
 
-template <int D, bool SH>
+// The key parts of a row group brought together at the end (every copy landed,
+// nothing left to read in the ring): parts 1 .. C::P-1 put their reference, row
+// sum (of both lanes of a row) and O in LDS, part 0 merges them in order into
+// its own.  True in part 0.
+template <class C>
+__device__ __forceinline__ bool merge_parts(unsigned char *smem, int rg, int part, int lane,
+                                            float &m_ref, float &l_tot, f32x16 (&oacc)[C::NE]) {
+  auto area = [&](int p) __attribute__((always_inline)) {
+    return smem + ((p - 1) * C::R + rg) * C::PART_BYTES;
+  };
+  constexpr int kScalars = C::NE * 4 * 1024;
+  barrier_no_fence();
+  if (part > 0) {
+    unsigned char *a = area(part);
+#pragma unroll
+    for (int n = 0; n < C::NE; ++n)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        *reinterpret_cast<f32x4 *>(a + (n * 4 + g) * 1024 + 16 * lane) =
+            f32x4{oacc[n][4 * g], oacc[n][4 * g + 1], oacc[n][4 * g + 2], oacc[n][4 * g + 3]};
+    *reinterpret_cast<float *>(a + kScalars + 4 * lane) = m_ref;
+    *reinterpret_cast<float *>(a + kScalars + 256 + 4 * lane) = l_tot;
+  }
+  __syncthreads();
+  if (part > 0) return false;
+  float m_all = m_ref, pm[C::P], wt[C::P];
+  pm[0] = m_ref;
+#pragma unroll
+  for (int p = 1; p < C::P; ++p) {
+    pm[p] = *reinterpret_cast<const float *>(area(p) + kScalars + 4 * lane);
+    m_all = fmaxf(m_all, pm[p]);
+  }
+#pragma unroll
+  for (int p = 0; p < C::P; ++p) wt[p] = pm[p] == -INFINITY ? 0.f : fast_exp2(pm[p] - m_all);
+  m_ref = m_all;
+  l_tot *= wt[0];
+#pragma unroll
+  for (int n = 0; n < C::NE; ++n)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) oacc[n][r] *= wt[0];
+#pragma unroll
+  for (int p = 1; p < C::P; ++p) {
+    l_tot = fmaf(wt[p], *reinterpret_cast<const float *>(area(p) + kScalars + 256 + 4 * lane),
+                 l_tot);
+#pragma unroll
+    for (int n = 0; n < C::NE; ++n)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const f32x4 z =
+            *reinterpret_cast<const f32x4 *>(area(p) + (n * 4 + g) * 1024 + 16 * lane);
+#pragma unroll
+        for (int y = 0; y < 4; ++y) oacc[n][4 * g + y] = fmaf(wt[p], z[y], oacc[n][4 * g + y]);
+      }
+  }
+  return true;
+}
+
+template <int D, bool SH, int P>
 __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
     const RowView qv, const RowView kv, const RowView vv, const RowView ov,
     float *__restrict__ lse, int S, int Hl, int n_rep, int heads_total, int qtiles,
     float c /* scale * log2(e) */) {
-  using C = FwdCfg<D>;
+  using C = FwdCfg<D, P>;
+  constexpr int kStages = C::STAGES, kPD = C::PD;
   using T = LdsTile<C::LW>;
   // LDS: the K tiles of the kStages ring stages, then their V tiles, so that
   // a stage's K and V tiles sit at the same offset from two fixed bases.
@@ -110,8 +179,9 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
   const int qt = qtiles - 1 - L / heads_total;
   const int hb = L % heads_total;
   const int beta = hb / Hl, h = hb % Hl, kvh = h / n_rep;
-  const int q0 = qt * kBM;
-  const int wrow0 = q0 + 32 * w;
+  const int q0 = qt * C::BM;
+  const int rg = w % C::R, part = w / C::R;  // row group, key part
+  const int wrow0 = q0 + 32 * rg;
   const int row = wrow0 + l32;
 
   const uint32_t q_row_bytes = qv.row_elems * 2, kv_row_bytes = kv.row_elems * 2;
@@ -139,8 +209,8 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
   // drain the prefetched tiles.
   wait_vmcnt<0>();
 
-  const int kv_end = min(S, q0 + kBM);
-  const int nt = (kv_end + kBN - 1) / kBN;
+  const int kv_end = min(S, q0 + C::BM);
+  const int nt = (kv_end + C::BT - 1) / C::BT;
 
   uint32_t g_off[C::DMA_PER_WAVE];
 #pragma unroll
@@ -173,6 +243,24 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
       buf_load16_lds_async(rv, base + g_off[i], lds_off + kVRegion);
     }
   };
+  // P = 2: K and V apart.  Tile t's scores are formed one iteration before its
+  // P V, so K runs one tile ahead of V and two stages of each are enough.
+  auto load_one = [&](int t, const RowView &view, u32x4 r, uint32_t region)
+                      __attribute__((always_inline)) {
+    uint32_t base = (uint32_t)(t * C::BT) * kv_row_bytes;
+    if constexpr (SH) {  // the tile's shard (shard rows are a multiple of 256)
+      uint32_t left;
+      r = make_rsrc_words(view_row<true, const uint16_t>(view, beta, t * C::BT, kvh, D, left),
+                          left * kv_row_bytes);
+      base = 0;
+    }
+    const uint32_t ks = smem_lds + (t % kStages) * C::TILE_BYTES + region;
+#pragma unroll
+    for (int i = 0; i < C::DMA_PER_WAVE; ++i)
+      buf_load16_lds_async(r, base + g_off[i], ks + (w * C::DMA_PER_WAVE + i) * 1024);
+  };
+  auto load_k = [&](int t) __attribute__((always_inline)) { load_one(t, kv, rk, 0); };
+  auto load_v = [&](int t) __attribute__((always_inline)) { load_one(t, vv, rv, kVRegion); };
   // Wait until this wave's loads of tile t landed, with `ahead` later tiles
   // (2 * DMA_PER_WAVE loads each) still in flight.
   auto wait_tile = [&](int ahead) {
@@ -184,10 +272,11 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
   // LDS offsets of this lane's operand reads (fixed across tiles).
   // A of S^T: K row 32m + l32, chunk 2s + hh.  The swizzle depends on the
   // row modulo 16 only, so row 32 + r sits 32 rows further on.
+  const int part_off = part * kBN * T::ROW_BYTES;  // first row of the wave's keys
   int k_off[C::NS];
 #pragma unroll
   for (int s = 0; s < C::NS; ++s) {
-    k_off[s] = T::off(l32, 2 * s + hh);
+    k_off[s] = T::off(l32, 2 * s + hh) + part_off;
     asm volatile("" : "+v"(k_off[s]));  // keep in a register, do not recompute per tile
   }
   // A of O^T: V^T rows e = 32n + l32, keys 16*s2 + 4hh + {0..3} and + 8.
@@ -199,7 +288,8 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
 #pragma unroll
     for (int x = 0; x < 2; ++x) {
       v_off[n][x] =
-          kVRegion + tr_piece_off<C::LW>(4 * hh + 8 * x, 32 * n + 16 * ((lane >> 4) & 1), lane);
+          kVRegion + part_off +
+          tr_piece_off<C::LW>(4 * hh + 8 * x, 32 * n + 16 * ((lane >> 4) & 1), lane);
       asm volatile("" : "+v"(v_off[n][x]));
     }
 
@@ -210,13 +300,19 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
     for (int r = 0; r < 16; ++r) oacc[n][r] = 0.f;
   float m_ref = -INFINITY, l_run = 0.f;
 
-  for (int t = 0; t <= kPD && t < nt; ++t) load_tile(t);
+  if constexpr (P == 1) {
+    for (int t = 0; t <= kPD && t < nt; ++t) load_tile(t);
+  } else {
+    load_k(0);
+    load_v(0);
+    if (nt > 1) load_k(1);
+  }
 
   // One tile: scores, softmax update, P V.  MASK only for tiles that can
   // hold keys past some row of the workgroup (the diagonal band).
   auto tile = [&](int t, auto mask_tag) {
     constexpr bool MASK = decltype(mask_tag)::value;
-    const int j0 = t * kBN;
+    const int j0 = t * C::BT + kBN * part;
     const unsigned char *Ks = smem + (t % kStages) * C::TILE_BYTES;
     const unsigned char *Vs = Ks;  // v_off holds the V region's base
 
@@ -266,7 +362,8 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
     if (__builtin_amdgcn_ballot_w64(grow)) {  // wave-uniform, rare after the first tiles
       asm volatile("" ::: "memory");  // keep this a real branch (no if-conversion)
       const float m_new = grow ? mx : m_ref;
-      const float alpha = fast_exp2(m_ref - m_new);
+      // P = 2: a row of which this part has seen no key yet keeps its -inf
+      const float alpha = P == 1 || grow ? fast_exp2(m_ref - m_new) : 1.f;
       m_ref = m_new;
       l_run *= alpha;
 #pragma unroll
@@ -274,12 +371,13 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
 #pragma unroll
         for (int r = 0; r < 16; ++r) oacc[n][r] *= alpha;
     }
+    const float m_use = P > 1 && m_ref == -INFINITY ? 0.f : m_ref;  // no key yet: P = 0
     float psum = 0.f;
 #pragma unroll
     for (int m = 0; m < 2; ++m)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const float p = fast_exp2(fmaf(sacc[m][r], c, -m_ref));
+        const float p = fast_exp2(fmaf(sacc[m][r], c, -m_use));
         sacc[m][r] = p;
         psum += p;
       }
@@ -317,10 +415,23 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
   // t - 1, after a barrier that every wave passes only once it has finished
   // with tile t - 1.  Before the barrier a wave waits for its own copies of
   // the tile it is about to read, with `ahead` later tiles left in flight.
+  // P = 2: iteration t of the pipelined loop reads K of tile t+1 and V of tile
+  // t, which its own wait (for every copy) made visible, and issues K of tile
+  // t+2 and V of tile t+1 into the stages of K of t and V of t-1, which every
+  // wave has finished with.  The one masked tile is the last: nothing is
+  // issued past it.
   auto make_visible = [&](int ahead, int issue) __attribute__((always_inline)) {
-    wait_tile(ahead);
-    barrier_no_fence();
-    if (issue < nt) load_tile(issue);
+    if constexpr (P == 1) {
+      wait_tile(ahead);
+      barrier_no_fence();
+      if (issue < nt) load_tile(issue);
+    } else {
+      wait_vmcnt<0>();
+      barrier_no_fence();
+      const int t = issue - kPD - 1;
+      if (t + 2 < nt) load_k(t + 2);
+      if (t + 1 < nt) load_v(t + 1);
+    }
   };
 
   // Tiles before t_mask need no mask.  They run software-pipelined: while
@@ -329,7 +440,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
   // the row maxima of tile t+1 are formed, so that every stretch of the
   // wave's instruction stream mixes matrix and vector work.  The arithmetic
   // and its order per tile are those of `tile`: bit-identical results.
-  const int t_mask = min(nt, q0 / kBN);
+  const int t_mask = min(nt, q0 / C::BT);
   auto scores = [&](int t, f32x16 (&sc)[2]) __attribute__((always_inline)) {
     const unsigned char *Ks = smem + (t % kStages) * C::TILE_BYTES;
 #pragma unroll
@@ -498,46 +609,67 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
   };
   if (t_mask > 0) {
     f32x16 sa[2], sb[2];
-    make_visible(min(kPD, nt - 1), nt);  // tile 0; tile kPD + 1 is issued by iteration 0
+    if constexpr (P == 1) {
+      make_visible(min(kPD, nt - 1), nt);  // tile 0; tile kPD + 1 is issued by iteration 0
+    } else {
+      wait_vmcnt<0>();  // K of tile 0 (and every other copy)
+      barrier_no_fence();
+    }
     scores(0, sa);
     move_reference(row_max(sa));
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
-    using I2 = std::integral_constant<int, 2>;
-    using I3 = std::integral_constant<int, 3>;
-    static_assert(kStages == 4, "the unrolled loop assumes four ring stages");
     int t = 0;
-    for (; t + 4 < t_mask; t += 4) {  // t % 4 == 0: every stage offset a constant
-      pipelined(t, I0{}, sa, sb);
-      pipelined(t + 1, I1{}, sb, sa);
-      pipelined(t + 2, I2{}, sa, sb);
-      pipelined(t + 3, I3{}, sb, sa);
-    }
-    // 1 to 4 unmasked tiles left, the last of them without scores to start
-    if (t + 1 < t_mask) {
-      pipelined(t, I0{}, sa, sb);
-      if (t + 2 < t_mask) {
+    if constexpr (P == 1) {
+      using I2 = std::integral_constant<int, 2>;
+      using I3 = std::integral_constant<int, 3>;
+      static_assert(P > 1 || kStages == 4, "the unrolled loop assumes four ring stages");
+      for (; t + 4 < t_mask; t += 4) {  // t % 4 == 0: every stage offset a constant
+        pipelined(t, I0{}, sa, sb);
         pipelined(t + 1, I1{}, sb, sa);
-        if (t + 3 < t_mask) {
-          pipelined(t + 2, I2{}, sa, sb);
-          pipelined_last(t + 3, sb);
+        pipelined(t + 2, I2{}, sa, sb);
+        pipelined(t + 3, I3{}, sb, sa);
+      }
+      // 1 to 4 unmasked tiles left, the last of them without scores to start
+      if (t + 1 < t_mask) {
+        pipelined(t, I0{}, sa, sb);
+        if (t + 2 < t_mask) {
+          pipelined(t + 1, I1{}, sb, sa);
+          if (t + 3 < t_mask) {
+            pipelined(t + 2, I2{}, sa, sb);
+            pipelined_last(t + 3, sb);
+          } else {
+            pipelined_last(t + 2, sa);
+          }
         } else {
-          pipelined_last(t + 2, sa);
+          pipelined_last(t + 1, sb);
         }
       } else {
-        pipelined_last(t + 1, sb);
+        pipelined_last(t, sa);
       }
     } else {
-      pipelined_last(t, sa);
+      for (; t + 2 < t_mask; t += 2) {  // t % 2 == 0
+        pipelined(t, I0{}, sa, sb);
+        pipelined(t + 1, I1{}, sb, sa);
+      }
+      if (t + 1 < t_mask) {
+        pipelined(t, I0{}, sa, sb);
+        pipelined_last(t + 1, sb);
+      } else {
+        pipelined_last(t, sa);
+      }
     }
   }
   for (int t = t_mask; t < nt; ++t) {  // the diagonal band, masked
     make_visible(min(kPD, nt - 1 - t), t + kPD + 1);
-    if (t * kBN <= wrow0 + 31) tile(t, std::true_type{});  // wave-uniform
+    if (t * C::BT + kBN * part <= wrow0 + 31) tile(t, std::true_type{});  // wave-uniform
   }
 
   // oacc[n][r] = O^T[e = 32n + 8(r/4) + 4hh + r%4][query row] (unnormalised)
-  const float l_tot = pair_sum(l_run);
+  float l_tot = pair_sum(l_run);
+  if constexpr (P > 1) {
+    if (!merge_parts<C>(smem, rg, part, lane, m_ref, l_tot, oacc)) return;
+  }
   if (row < S) {
     const float inv = 1.f / l_tot;
     uint32_t o_left;
@@ -558,16 +690,16 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
 }
 
 // ---------------------------------------------------------------- split form
-// The forward of shares too small to fill the GPU with 256-row workgroups:
-// the 8 waves are R row groups of 32 query rows times P = 8 / R key parts, and
-// part p takes keys 32p .. 32p+31 of each tile of 32 P keys.  A workgroup is
+// The forward of the smallest shares (and of small ones at d = 64): the 8
+// waves are R row groups of 32 query rows times P = 8 / R key parts, and part p
+// takes keys 32p .. 32p+31 of each tile of 32 P keys.  A workgroup is
 // then 32 R rows, with the same two waves per SIMD and the same products per
 // tile, for a half or a quarter of the rows and of the key loop's length.
-// Each wave runs its own online softmax over its keys; at the end parts 1 ..
-// P-1 put (reference, row sum, O) in LDS and part 0 merges them in order.  A
-// wave's tile is not software-pipelined: the loop is short.
-template <int D, int R>
+// Each wave runs its own online softmax over its keys, merged at the end.  A
+// wave's tile is not software-pipelined: it is 32 keys, and the loop is short.
+template <int D, int RG>
 struct SplitCfg {
+  static constexpr int R = RG;
   static constexpr int DC = HeadDim<D>::DC;
   static constexpr int LW = HeadDim<D>::LW;
   static constexpr int P = kWaves / R;
@@ -580,8 +712,6 @@ struct SplitCfg {
   static constexpr int NE = DC / 32;
   static constexpr int CPR = LW / 8;
   static constexpr int DMA_PER_WAVE = BN * CPR / kThreads;
-  // A part's row of the merge area: NE*4 register groups of O, the reference
-  // and the row sum, 1 KB (64 lanes x 16 B) each group, 256 B each scalar.
   static constexpr int PART_BYTES = NE * 4 * 1024 + 512;
   static_assert((P - 1) * R * PART_BYTES <= LDS_BYTES, "the merge area fits the ring");
 };
@@ -791,40 +921,8 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_split_kernel(
     tile(t, t % kSt, std::true_type{});
   }
 
-  // Merge (every copy landed, nothing left to read in the ring).
   float l_tot = pair_sum(l_run);
-  auto area = [&](int p) __attribute__((always_inline)) {
-    return smem + ((p - 1) * R + rg) * C::PART_BYTES;
-  };
-  barrier_no_fence();
-  if (part > 0) {
-    unsigned char *a = area(part);
-#pragma unroll
-    for (int n = 0; n < C::NE; ++n)
-#pragma unroll
-      for (int g = 0; g < 4; ++g)
-        *reinterpret_cast<f32x4 *>(a + (n * 4 + g) * 1024 + 16 * lane) =
-            f32x4{oacc[n][4 * g], oacc[n][4 * g + 1], oacc[n][4 * g + 2], oacc[n][4 * g + 3]};
-    *reinterpret_cast<float *>(a + C::NE * 4096 + 4 * lane) = m_ref;
-    *reinterpret_cast<float *>(a + C::NE * 4096 + 256 + 4 * lane) = l_tot;
-  }
-  __syncthreads();
-  if (part > 0 || row >= S) return;
-  float m_all = m_ref;
-  float pm[C::P], wt[C::P];
-  pm[0] = m_ref;
-#pragma unroll
-  for (int p = 1; p < C::P; ++p) {
-    pm[p] = *reinterpret_cast<const float *>(area(p) + C::NE * 4096 + 4 * lane);
-    m_all = fmaxf(m_all, pm[p]);
-  }
-#pragma unroll
-  for (int p = 0; p < C::P; ++p) wt[p] = pm[p] == -INFINITY ? 0.f : fast_exp2(pm[p] - m_all);
-  l_tot *= wt[0];
-#pragma unroll
-  for (int p = 1; p < C::P; ++p)
-    l_tot = fmaf(wt[p], *reinterpret_cast<const float *>(area(p) + C::NE * 4096 + 256 + 4 * lane),
-                 l_tot);
+  if (!merge_parts<C>(smem, rg, part, lane, m_ref, l_tot, oacc) || row >= S) return;
   const float inv = 1.f / l_tot;
   uint32_t o_left;
   uint16_t *ob = view_row<SH, uint16_t>(ov, beta, q0, h, D, o_left) +
@@ -834,36 +932,29 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_split_kernel(
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
       if (32 * n + 8 * g >= D) continue;  // padding columns
-      f32x4 x;
-#pragma unroll
-      for (int y = 0; y < 4; ++y) x[y] = oacc[n][4 * g + y] * wt[0];
-#pragma unroll
-      for (int p = 1; p < C::P; ++p) {
-        const f32x4 z =
-            *reinterpret_cast<const f32x4 *>(area(p) + (n * 4 + g) * 1024 + 16 * lane);
-#pragma unroll
-        for (int y = 0; y < 4; ++y) x[y] = fmaf(wt[p], z[y], x[y]);
-      }
       *reinterpret_cast<u32x2 *>(ob + 32 * n + 8 * g + 4 * hh) =
-          u32x2{pack_bf16x2(x[0] * inv, x[1] * inv), pack_bf16x2(x[2] * inv, x[3] * inv)};
+          u32x2{pack_bf16x2(oacc[n][4 * g] * inv, oacc[n][4 * g + 1] * inv),
+                pack_bf16x2(oacc[n][4 * g + 2] * inv, oacc[n][4 * g + 3] * inv)};
     }
   if (hh == 0)
-    lse[((size_t)beta * Hl + h) * S + row] = (m_all + fast_log2(l_tot)) * 0.69314718055994531f;
+    lse[((size_t)beta * Hl + h) * S + row] = (m_ref + fast_log2(l_tot)) * 0.69314718055994531f;
 }
 
-// Row groups of a workgroup: 8 (attn_fwd_kernel), 4 or 2.  Up to the lines
-// below (in W = b * Hl * S query rows) the 256-row workgroups, causal and so
-// of very different lengths, leave CUs idle; past them the pipelined kernel's
-// higher rate wins.  At d = 64 two split workgroups fit a CU, so the line
-// lies higher.  Forward, us on MI355X, R = 8, 4, 2 (110 shares of 256 to 45K
-// rows): d = 128: W = 4.4K 18, 15, 11; 16K 45, 32, 22; 36K 37, 28, 33; 50K
-// 123, 96, 103; 66K (8 heads, S = 8K) 186, 125, -; 76K 215, 207, 226; 86K 137,
-// 141, 156; 110K 356, 401, 433.  d = 64: 28K 53, 37, 26; 45K 85, 60, 58; 79K 55,
-// 48, 64; 113K 331, 319, 394; 131K 290, 301, -.
+// Row groups of a workgroup: 8 (attn_fwd_kernel, P = 1), 4 (P = 2; at d = 64
+// the split kernel) or 2 (the split kernel).  Up to the lines below, in W = b *
+// Hl * S query rows, 256-row workgroups, causal and so of very different
+// lengths, leave CUs idle; past them the wider workgroups' higher rate wins:
+// a K or V tile feeds more products.  Forward, us on MI355X for 8 | 4 | 2:
+// d = 128: W = 16K 45 | - | 22; 31K 146 | 93 | 76; 37K 339 | 221 | 216; 40K 370 |
+// 243 | 248; 56K 280 | 197 | 241; 75K 108 | 105 | 122; 87K 149 | 150 | 175; 183K 932 |
+// 954 | 1165.  d = 96: 81K 103 | 98 | 118; 108K 373 | 392 | 478.  d = 64, where
+// VALU work bounds both and two split workgroups fit a CU: 35K 127 | 87 | 68;
+// 43K 31 | 24 | 28; 76K 190 | 160 | 184; 107K 216 | 216 | 266; 115K 135 | 141 |
+// 185; 172K 274 | 261 | 358.
 int row_groups(const AttnShape &s) {
   const long long rows = (long long)s.b * s.Hl * s.S;
-  if (rows <= 35840) return 2;
-  return rows <= (s.d == 64 ? 122880 : 73728) ? 4 : 8;
+  if (rows <= 38400) return 2;
+  return rows <= (s.d == 64 ? 106496 : 81920) ? 4 : 8;
 }
 
 }  // namespace
@@ -887,8 +978,11 @@ hipError_t launch_attn_fwd(const RowView &q, const RowView &k, const RowView &v,
     constexpr bool SH = decltype(sh)::value;
     switch (R) {
       case 2: go(attn_fwd_split_kernel<D, SH, 2>); break;
-      case 4: go(attn_fwd_split_kernel<D, SH, 4>); break;
-      default: go(attn_fwd_kernel<D, SH>); break;
+      case 4:
+        if constexpr (D == 64) go(attn_fwd_split_kernel<D, SH, 4>);
+        else go(attn_fwd_kernel<D, SH, 2>);
+        break;
+      default: go(attn_fwd_kernel<D, SH, 1>); break;
     }
   };
   auto by_dim = [&](auto sh) {

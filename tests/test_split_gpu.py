@@ -36,8 +36,8 @@ CASES = [  # b, S, Hl, Hkl, d
     (1, 4609, 4, 2, 128), (3, 1500, 6, 2, 96), (1, 4097, 8, 4, 80),
     (2, 2304, 8, 2, 128), (2, 2305, 8, 2, 128),
     # forward rows per workgroup: 64 | 128 and 128 | 256
-    (1, 4480, 8, 2, 128), (1, 4481, 8, 2, 96), (1, 9216, 8, 2, 80), (1, 9217, 8, 2, 80),
-    (3, 5120, 8, 4, 64), (3, 5121, 8, 4, 64),
+    (1, 4800, 8, 2, 128), (1, 4801, 8, 2, 96), (1, 10240, 8, 2, 80), (1, 10241, 8, 2, 80),
+    (2, 6656, 8, 4, 64), (2, 6657, 8, 4, 64), (160, 130, 4, 2, 128), (300, 128, 1, 1, 96),
 ]
 
 
