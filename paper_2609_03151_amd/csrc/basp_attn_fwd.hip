@@ -34,7 +34,8 @@
 //     between the P V products of t, one product per slot with its operand
 //     read two slots ahead.  Every stretch of a wave's instruction stream
 //     thus mixes matrix and vector work; the arithmetic and its order per
-//     tile are unchanged (bit-identical results).
+//     tile are unchanged (bit-identical results).  Below d = 128 the row sum
+//     goes with the exponentials and stands guard for the row maxima (kGuard).
 //   * LDS holds the K tiles of the four ring stages, then their V tiles, and
 //     the pipelined loop is unrolled over the four stages: every operand
 //     address is a lane's fixed offset plus an instruction immediate, with
@@ -70,6 +71,9 @@ constexpr int kThreads = 512;
 constexpr int kWaves = 8;
 constexpr int kBN = 64;           // keys per wave and tile
 constexpr float kRescaleSlack = 8.f;  // log2 headroom before the reference max moves
+// GUARD: a lane's sum of a tile's P past which the row maxima are looked for.
+// P up to about 2^16 is as exact as P <= 1, in bf16 and in the fp32 sums.
+constexpr float kGuardSum = 65536.f;
 // Instruction classes of __builtin_amdgcn_sched_group_barrier.
 constexpr int kSchedValu = 0x002;
 constexpr int kSchedMfma = 0x008;
@@ -165,6 +169,13 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
     float c /* scale * log2(e) */) {
   using C = FwdCfg<D, P>;
   constexpr int kStages = C::STAGES, kPD = C::PD;
+  // Whether the pipelined loop leaves the row maxima out and lets the row sums,
+  // which it needs anyway, say when the reference has been outgrown: 18 vector
+  // instructions less per tile.  Forward at S = 16K, 8 heads on 2: d = 64 340 ->
+  // 327 us, 96 395 -> 386, 80 360 -> 351.  At d = 128 the registers that the
+  // rare path needs are not there (230 spills, 0.5% slower), and with P = 2 K of
+  // the tile is gone by then.
+  constexpr bool kGuard = P == 1 && D < 128;
   using T = LdsTile<C::LW>;
   // LDS: the K tiles of the kStages ring stages, then their V tiles, so that
   // a stage's K and V tiles sit at the same offset from two fixed bases.
@@ -498,7 +509,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
     for (int m = 0; m < 2; ++m)
 #pragma unroll
       for (int r = 0; r < 16; ++r) psum += sc[m][r];
-    l_run += psum;
+    return psum;
   };
   auto pv = [&](int t, const bf16x8 (&pf)[kBN / 16]) __attribute__((always_inline)) {
     const unsigned char *Vs = smem + (t % kStages) * C::TILE_BYTES;
@@ -510,6 +521,27 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
                                     v_off[n][1] + s2 * 16 * T::ROW_BYTES);
         oacc[n] = mfma32x32x16(a, pf[s2], oacc[n]);
       }
+  };
+  // kGuard, before P V of tile t: where a lane's sum says that the reference
+  // has been outgrown (or is no number: P overflowed, or a score is NaN) the
+  // tile's scores are formed again, K of tile t being still in its stage, and
+  // P after the reference moved as in `tile`.
+  auto guard = [&](int t, f32x16 (&cur)[2], bf16x8 (&pf)[kBN / 16], float &psum)
+                   __attribute__((always_inline)) {
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(psum <= kGuardSum)) != 0, 0)) {
+      asm volatile("" ::: "memory");
+      const unsigned char *Ks = smem + (t % kStages) * C::TILE_BYTES;
+#pragma unroll
+      for (int g = 0; g < 2 * C::NS; ++g) {
+        const bf16x8 a =
+            *reinterpret_cast<const bf16x8 *>(Ks + k_off[g / 2] + (g % 2) * 32 * T::ROW_BYTES);
+        cur[g % 2] = mfma32x32x16(a, qf[g / 2], g < 2 ? f32x16{} : cur[g % 2]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      move_reference(row_max(cur));
+      exps(cur, pf);
+      psum = row_sum(cur);
+    }
   };
   // Iteration t of the pipelined loop, tile t+1 unmasked: `cur` holds the
   // scores of tile t (reference already moved for them); the scores of tile
@@ -523,6 +555,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
     make_visible(min(1, nt - 2 - t), t + kPD + 1);  // tile t+1 readable, t+2 in flight
     asm volatile("" : "+v"(m_ref));  // keep the exponent arguments here
     bf16x8 pf[kBN / 16];
+    float psum = 0.f, mx = -INFINITY;
     // Block X: scores of tile t+1 (16 products), exponentials of tile t, at
     // raised issue priority: of the two waves of a SIMD, the one in this
     // block keeps the matrix unit while the other is in block Y.
@@ -547,6 +580,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
         for (int e = 32 * g / NG; e < 32 * (g + 1) / NG; ++e) {
           const int mm = e / 16, r = e % 16;
           cur[mm][r] = fast_exp2(fmaf(cur[mm][r], c, -m_ref));
+          if constexpr (kGuard) psum += cur[mm][r];
           if (r % 8 == 7) {
             const int b8 = r - 7;
             pf[2 * mm + b8 / 8] = as_bf16x8(u32x4{pack_bf16x2(cur[mm][b8 + 0], cur[mm][b8 + 1]),
@@ -560,7 +594,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
     }
     wave_priority<0>();
     // Block Y: P V of tile t (16 products), row sum of t, row maxima of t+1.
-    float psum = 0.f, mx = -INFINITY;
+    if constexpr (kGuard) guard(t, cur, pf, psum);
     {
       constexpr int NG = C::NE * (kBN / 16);
       const unsigned char *Vs = smem + ST * C::TILE_BYTES;
@@ -578,15 +612,18 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
         if (g + kPf < NG) read(g + kPf);
         const int n = g / (kBN / 16), s2 = g % (kBN / 16);
         oacc[n] = mfma32x32x16(op[g], pf[s2], oacc[n]);
+        if constexpr (!kGuard) {
 #pragma unroll
-        for (int e = 32 * g / NG; e < 32 * (g + 1) / NG; ++e) psum += cur[e / 16][e % 16];
+          for (int e = 32 * g / NG; e < 32 * (g + 1) / NG; ++e) psum += cur[e / 16][e % 16];
 #pragma unroll
-        for (int e = 32 * g / NG; e < 32 * (g + 1) / NG; ++e) mx = fmaxf(mx, nxt[e / 16][e % 16]);
+          for (int e = 32 * g / NG; e < 32 * (g + 1) / NG; ++e) mx = fmaxf(mx, nxt[e / 16][e % 16]);
+        }
         __builtin_amdgcn_sched_barrier(0);
       }
     }
     l_run += psum;
-    move_reference(pair_max(mx) * c);  // after P V of tile t, before the exponentials of t+1
+    if constexpr (!kGuard)
+      move_reference(pair_max(mx) * c);  // after P V of tile t, before the exponentials of t+1
   };
   // The last unmasked tile t: no scores to start.
   auto pipelined_last = [&](int t, f32x16 (&cur)[2]) __attribute__((always_inline)) {
@@ -594,9 +631,15 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
     asm volatile("" : "+v"(m_ref));
     bf16x8 pf[kBN / 16];
     exps(cur, pf);
+    float psum = 0.f;
+    if constexpr (kGuard) {
+      psum = row_sum(cur);
+      guard(t, cur, pf, psum);
+    }
     __builtin_amdgcn_sched_barrier(0);
     pv(t, pf);
-    row_sum(cur);
+    if constexpr (!kGuard) psum = row_sum(cur);
+    l_run += psum;
     __builtin_amdgcn_sched_group_barrier(kSchedDsRead, 4, 0);
 #pragma unroll
     for (int i = 0; i < C::NE * (kBN / 16) - 2; ++i) {

@@ -6,10 +6,11 @@ partial sums of dK and dV per key): uneven parts, ragged lengths, parts with
 one chunk, chunks with one part, b > 1, each head dim.  Its dQ pass gives a
 workgroup 256, 128 or 64 query rows by the share's rows (b * Hl * S): each
 width on both sides of its lines, ragged and shorter than one tile.  The
-forward gives a workgroup 256, 128 or 64 query rows likewise; its split kernels
-are also run on scores that grow along the sequence (the reference of every
-key part moves, parts of very different weight), on rows most key parts never
-reach, and in place on the shard buffers."""
+forward gives a workgroup 256, 128 or 64 query rows likewise; each width is also
+run on scores that grow or jump along the sequence (running references that
+move, key parts of very different weight, P past the range of fp32 until the
+reference has followed), on rows most key parts never reach, and in place on
+the shard buffers."""
 import math
 
 import pytest
@@ -92,18 +93,24 @@ def test_split_attention_matches_fp64(b, S, Hl, Hkl, d):
 @pytest.mark.parametrize("b,S,Hl,Hkl,d", [
     (1, 1000, 4, 1, 128), (2, 700, 2, 2, 64),   # 64 rows per workgroup
     (1, 5000, 8, 1, 128), (1, 5000, 8, 1, 80),  # 128
+    (8, 2000, 7, 1, 64), (8, 2000, 7, 1, 80), (8, 2000, 7, 1, 96), (8, 2000, 7, 1, 128),  # 256
 ])
-@pytest.mark.parametrize("peak", ["late", "early"])
-def test_split_forward_parts_of_unlike_weight(b, S, Hl, Hkl, d, peak):
-    """Scores that rise (or fall) along the keys by tens of units: each key
-    part's running reference moves many times, and a row's parts differ in
-    weight by many orders of magnitude when they are merged."""
+@pytest.mark.parametrize("peak", ["late", "early", "jumps"])
+def test_forward_references_that_move(b, S, Hl, Hkl, d, peak):
+    """Scores that rise (or fall) along the keys by tens of units, or jump by
+    hundreds at single keys (exp2 of the difference is past fp32's range): each
+    running reference moves many times, and a row's key parts differ in weight
+    by many orders of magnitude when they are merged."""
     log(f"[split ramp] b={b} S={S} Hl={Hl} Hkl={Hkl} d={d} {peak}")
     g = torch.Generator("cuda").manual_seed(S + d)
     mk = lambda n: torch.randn((b, S, n, d), generator=g, device="cuda")
     q, k, v, do = mk(Hl), mk(Hkl), mk(Hkl), mk(Hl)
     ramp = torch.linspace(0, 40, S, device="cuda")[None, :, None]
-    q[..., 0], k[..., 0] = d ** 0.25, (ramp if peak == "late" else -ramp) * d ** 0.25
+    if peak == "jumps":  # 0 but for a handful of keys, each 150 above the one before
+        ramp = torch.zeros_like(ramp)
+        for i, at in enumerate((70, S // 5, S // 2 + 1, 3 * S // 4, S - 100)):
+            ramp[:, at] = 150.0 * (i + 1)
+    q[..., 0], k[..., 0] = d ** 0.25, (-ramp if peak == "early" else ramp) * d ** 0.25
     q, k, v, do = (t.to(torch.bfloat16) for t in (q, k, v, do))
     o, lse = basp.attn_fwd(q, k, v)
     ref = _reference(q, k, v, do, d ** -0.5)
