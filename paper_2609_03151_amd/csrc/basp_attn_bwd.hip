@@ -143,7 +143,7 @@ struct BwdArgs {
   uint32_t plane_bytes;   // np - lp
   uint32_t dq_blocks;     // workgroups of the dQ pass
   int b, S, Sp, Hl, Hkl, n_rep;
-  int nchunks, chunk_tiles, nsplits;
+  int nchunks, chunk_tiles, nsplits, keys_first;
   float c, scale;         // scale * log2(e), scale
 };
 
@@ -850,9 +850,10 @@ __device__ __forceinline__ void bwd_dq_tile(const BwdArgs &a, int L, unsigned ch
 
 // ---------------------------------------------------------------- bwd_main
 // Both passes in one launch: neither reads what the other writes, so the dQ
-// tiles (heaviest first) and then the key units (full ones, then the diagonal
-// ones, longest first) form one list, and the short units at its end fill the
-// CUs that the long ones leave idle.  Workgroups [0, dq_blocks) take dQ tiles.
+// tiles (heaviest first) and the key units (full ones, then the diagonal ones,
+// longest first) form one list, the kind with the longer units first
+// (bwd_keys_first), and the short units at its end fill the CUs that the long
+// ones leave idle.
 // Each pass alone leaves most CUs idle while its longest workgroups finish, up
 // to S = 16K with 8 query heads (one workgroup per CU, or fewer).  One launch
 // against two, the whole step on one MI355X: 8 heads of 128, S = 8K 740 -> 672
@@ -862,10 +863,13 @@ __global__ __launch_bounds__(kKvThreads, 1) void bwd_main_kernel(const BwdArgs a
   static_assert(kKvThreads == kDqThreads, "one workgroup size for both passes");
   constexpr int kKvLds = KvCfg<D>::LDS_BYTES, kDqLds = DqCfg<D, R>::STAGES * DqCfg<D, R>::STAGE_BYTES;
   __shared__ __attribute__((aligned(16))) unsigned char smem[kKvLds > kDqLds ? kKvLds : kDqLds];
-  if (blockIdx.x < a.dq_blocks)
-    bwd_dq_tile<D, SH, R>(a, (int)blockIdx.x, smem);
+  const uint32_t kv_blocks = gridDim.x - a.dq_blocks;
+  const uint32_t first = a.keys_first ? kv_blocks : a.dq_blocks;
+  const uint32_t i = blockIdx.x < first ? blockIdx.x : blockIdx.x - first;
+  if ((blockIdx.x < first) == (a.keys_first != 0))  // workgroup-uniform
+    bwd_kv_unit<D, SH>(a, (int)i, smem);
   else
-    bwd_kv_unit<D, SH>(a, (int)(blockIdx.x - a.dq_blocks), smem);
+    bwd_dq_tile<D, SH, R>(a, (int)i, smem);
 }
 
 template <int D, bool SH>
@@ -893,6 +897,7 @@ hipError_t launch_bwd_d(const RowView &q, const RowView &k, const RowView &v, co
   a.lp = lp, a.np = np, a.plane_bytes = plane_bytes;
   a.b = s.b, a.S = s.S, a.Sp = Sp, a.Hl = s.Hl, a.Hkl = s.Hkl, a.n_rep = n_rep;
   a.nchunks = ck.n, a.chunk_tiles = ck.T, a.nsplits = ck.splits;
+  a.keys_first = bwd_keys_first(s, ck);
   a.c = c, a.scale = s.scale;
   float *dv_part = nullptr, *dk_part = nullptr;
   const int parts = ck.n * ck.splits;

@@ -231,38 +231,45 @@ inline BwdChunks bwd_chunks_of(const AttnShape &s, int rows, int splits) {
 // than that leaves the other CUs idle while it runs (a kv head of 4 query
 // heads at S = 2048 is 128 steps per key tile for 8.5 per CU); a unit much
 // shorter pays its start, its 128 KB of partial sums and their reduction
-// (together about 4 steps) too often.  So a unit is about `mean` steps, below
-// 16 up to twice that, at least 8, and from 256 on half of it (measured on MI355X, backward, against
-// one unit per key tile and 2048-row chunk: 8 heads on 2 kv heads of 128, S =
-// 4096: 32-step units 133 us, 16: 145, 64: 135, unsplit 318; S = 16K:
-// 256-step units 1536 us, 512: 1576).  Query heads are split first, rows
-// next: long row chunks have fewer short diagonal units (32-step units at S =
-// 4096 as 2048 rows of one head 133 us, as 512 rows of four 142).  A unit of
-// all heads and a whole chunk of kv_chunk_rows, the old cut, stays where it is
-// no longer than that, and where the partial sums would need more than both
-// it and the static buffer of basp_attn_bwd_noalloc hold.
+// (together about 4 steps) too often.  The dQ pass, in the same launch, fills
+// the CUs beside the units, so a unit is about 2 `mean` steps, at least 8, from
+// a mean of 128 on 256 steps and from 512 on `mean` / 2.  Measured on MI355X,
+// backward, unit lengths in steps: 8 heads on 2 kv heads of 128, S = 4096 (mean
+// 33): 64 steps 128 us, 32 steps 133, 16 steps 145, uncut 318; 2 heads on 1, S =
+// 8192 (33): 131, 140, -, 308; 4 on 1 of 64, S = 4096 (16): 32 steps 48, 16 steps
+// 53, 64 steps 57; 8 on 2, S = 16K (520): 256 steps 1536, 512 steps 1576.
+// Up to a mean of 256 rows are cut first, down to 256, then query heads: the
+// fewest partial sums.  Past it whole chunks of the longest size
+// kv_chunk_rows allows are cut by query heads (S = 16K of 64: 8192 rows of two
+// heads 872 us, 4096 of four 885).  Chunks are of equal length: a short last one
+// is as many units as a long one (two sequences of 8564 rows, 7 heads on 1 of
+// 128, as 8192 + 372 rows of one head 970 us, as equal chunks of two heads 854).
+// Where the partial sums would need more than both one part per chunk of
+// kv_chunk_rows, the cut of old, and the static buffer of
+// basp_attn_bwd_noalloc hold, units are longer, at last that cut.
 inline BwdChunks bwd_chunks(const AttnShape &s) {
   const BwdChunks whole = bwd_chunks_of(s, kv_chunk_rows(s.S), 1);
   if (s.S < 1 || s.Hkl < 1) return whole;
   const int n_rep = s.Hl / s.Hkl;
   const long long ktiles = (s.S + kKvKeys - 1) / kKvKeys;
   const long long mean = (long long)s.b * s.Hl * ktiles * (ktiles + 1) / kBwdCus;
-  long long steps = mean;
-  if (mean < 16) steps = mean < 4 ? 8 : mean < 8 ? 2 * mean : 16;
-  if (mean > 128) steps = mean < 256 ? 128 : mean / 2;
-  // Whole heads over the longest chunks kv_chunk_rows allows, of equal length
-  // (a short last chunk is as many units as a long one: two sequences of 8564
-  // rows, 7 heads on 1 of 128, as 8192 + 372 rows of one head 970 us, equal
-  // chunks of two heads 854 us), or, where one such unit would be too long, one
-  // head over shorter chunks.
-  const long long cap = kv_chunk_rows(s.S) > 8192 ? kv_chunk_rows(s.S) : 8192, want = steps * 64;
+  const long long steps = mean < 4 ? 8 : mean <= 128 ? 2 * mean : mean <= 512 ? 256 : mean / 2;
+  const long long cap = kv_chunk_rows(s.S) > 8192 ? kv_chunk_rows(s.S) : 8192;
   auto equal_rows = [&](long long longest) {
     const int n = (int)((s.S + longest - 1) / longest);
     return ((s.S + n - 1) / n + kKvKeys - 1) / kKvKeys * kKvKeys;
   };
-  int rows = equal_rows(cap);
-  int heads = (int)((want + rows / 2) / rows < n_rep ? (want + rows / 2) / rows : n_rep);
-  if (heads <= 1 && 4 * want < 3LL * rows) rows = equal_rows(want);
+  const long long want = steps * 64;  // rows of one head in a unit
+  int rows, heads;
+  if (mean <= 256) {
+    long long r = (want / n_rep + kKvKeys / 2) / kKvKeys * kKvKeys;
+    r = r < 256 ? 256 : r > cap ? cap : r;
+    rows = equal_rows(r);
+    heads = (int)(want / rows < n_rep ? want / rows : n_rep);
+  } else {
+    rows = equal_rows(cap);
+    heads = (int)((want + rows / 2) / rows < n_rep ? (want + rows / 2) / rows : n_rep);
+  }
   if (heads < 1) heads = 1;
   const size_t whole_floats = bwd_workspace_floats(s, whole);
   const size_t limit = whole_floats > BASP_NOALLOC_SCRATCH_BYTES / sizeof(float)
@@ -286,6 +293,18 @@ inline BwdChunks bwd_chunks(const AttnShape &s) {
 inline int dq_row_groups(const AttnShape &s) {
   const long long rows = (long long)s.b * s.Hl * s.S;
   return rows <= 18432 ? 2 : rows <= 36864 ? 4 : 8;
+}
+
+// Whether the key pass's units go before the dQ tiles in the launch: the longer
+// kind first.  A dQ tile's longest loop, S / 64 tiles of 64 keys x 32 R rows x 3
+// products, is 3 R S / 1024 key-pass steps of 64 rows x 128 keys x 4 products.
+// (8 heads on 2 kv heads of 128, S = 4096, R = 4: units of 64 steps against 48
+// first 128 us, last 135; of 32 steps 147 and 134; 8 on 8, S = 8K, 128 steps
+// against 192: 466 and 413.)
+inline bool bwd_keys_first(const AttnShape &s, const BwdChunks &ck) {
+  const int n_rep = s.Hl / s.Hkl;
+  const long long unit = (long long)(ck.rows / 64) * ((n_rep + ck.splits - 1) / ck.splits);
+  return unit * 1024 > 3LL * dq_row_groups(s) * s.S;
 }
 
 // Never less than the whole-chunk cut takes, which can be more than the one

@@ -17,20 +17,22 @@ import pytest
 import torch
 
 import paper_2609_03151_amd as basp
-from parity import LSE_MAX_ABS, check_close, fp64_kv_head, log
+from parity import LSE_MAX_ABS, MAX_ABS, check_close, fp64_kv_head, log
 
 pytestmark = pytest.mark.gpu
 
 CASES = [  # b, S, Hl, Hkl, d
-    (1, 1024, 8, 1, 128),   # 2 chunks x 8 parts
-    (1, 1100, 7, 1, 96),    # ragged, one head per part
-    (2, 2048, 4, 1, 128),   # 2 chunks x 4 parts, b = 2
-    (1, 3000, 7, 1, 128),   # 3 chunks x 7 parts, ragged
+    (1, 1024, 8, 1, 128),   # 4 chunks x 4 parts
+    (1, 1100, 7, 1, 96),    # 5 chunks x 4 parts of 1 and 2 heads, ragged
+    (2, 2048, 4, 1, 128),   # 8 chunks, b = 2
+    (1, 3000, 7, 1, 128),   # 12 chunks, ragged
     (3, 769, 6, 2, 80),     # the last key tile one key long
     (1, 2113, 3, 3, 64),    # chunks only
     (1, 6000, 10, 2, 64),   # long ragged chunks
-    (1, 8192, 8, 2, 64),    # one chunk, parts only
-    (2, 9000, 10, 2, 128),  # uneven parts (3 and 2 heads)
+    (1, 8192, 8, 2, 64),    # key units before dQ tiles, 2 chunks
+    (1, 8192, 8, 8, 64),    # one unit per key tile
+    (2, 9000, 10, 2, 128),  # 2 chunks x 2 parts
+    (1, 11008, 20, 1, 64),  # parts of unlike size (6 and 7 heads)
     # dQ rows per workgroup: 64, then 128, then 256
     (1, 1, 1, 1, 128), (1, 63, 2, 1, 64), (1, 65, 1, 1, 96), (2, 129, 3, 3, 128),
     (1, 4608, 4, 2, 64), (1, 9216, 2, 1, 128),
@@ -85,8 +87,14 @@ def test_split_attention_matches_fp64(b, S, Hl, Hkl, d):
     torch.cuda.synchronize()
     ref = _reference(q, k, v, do, scale)
     f = lambda t: t.double().cpu().numpy()
+    # The bar on a key's dK and dV holds for up to 8 query heads on a kv head.
+    # Each head adds its own rounding of bf16 P and dS, independent of the
+    # others', so beyond 8 the sum's error grows with the root of their number.
+    kv_bar = MAX_ABS * max(1.0, (Hl / Hkl / 8) ** 0.5)
+    bars = {"LSE": dict(max_abs=LSE_MAX_ABS, mean_abs=LSE_MAX_ABS),
+            "dK": dict(max_abs=kv_bar), "dV": dict(max_abs=kv_bar)}
     for name, got, want in zip(("O", "LSE", "dQ", "dK", "dV"), (o, lse, dq, dk, dv), ref):
-        bar = dict(max_abs=LSE_MAX_ABS, mean_abs=LSE_MAX_ABS) if name == "LSE" else {}
+        bar = bars.get(name, {})
         check_close(name, f(got), f(want), **bar)
 
 
