@@ -30,19 +30,18 @@
 //     wave has just finished with, so two later tiles stay in flight.
 //   * tiles left of the diagonal band are software-pipelined inside each
 //     wave: the score products of tile t+1 are issued between the
-//     exponentials of tile t, and the row sum of t and row maxima of t+1
-//     between the P V products of t, one product per slot with its operand
-//     read two slots ahead.  Every stretch of a wave's instruction stream
-//     thus mixes matrix and vector work; the arithmetic and its order per
-//     tile are unchanged (bit-identical results).  Below d = 128 the row sum
-//     goes with the exponentials and stands guard for the row maxima (kGuard).
+//     exponentials of tile t, and the row sum of t between the P V products
+//     of t, one product per slot with its operand read two slots ahead.  Every
+//     stretch of a wave's instruction stream thus mixes matrix and vector work.
 //   * LDS holds the K tiles of the four ring stages, then their V tiles, and
 //     the pipelined loop is unrolled over the four stages: every operand
 //     address is a lane's fixed offset plus an instruction immediate, with
 //     no per-tile address arithmetic.
-//   * the running maximum used as the exponent reference only moves when a
-//     row's maximum grows by more than 8 (in log2 units): P <= 2^8 stays exact
-//     in bf16's relative precision and O is rescaled only on those tiles.
+//   * the exponent reference of a row starts as its first tile's maximum and
+//     follows only when it has been outgrown, so that O is rescaled on few
+//     tiles: by 16 (in log2 units) in the pipelined loop, which sees it in the
+//     row sums, by 8 elsewhere, where the maxima are formed.  P <= 2^16 is as
+//     exact in bf16 and in the fp32 sums as P <= 1.
 //   * tiles strictly below the workgroup's diagonal band run a loop without
 //     any masking code; band tiles are masked, and a wave skips band tiles
 //     past its last row.  The grid is one-dimensional, heaviest query tiles
@@ -71,9 +70,9 @@ constexpr int kThreads = 512;
 constexpr int kWaves = 8;
 constexpr int kBN = 64;           // keys per wave and tile
 constexpr float kRescaleSlack = 8.f;  // log2 headroom before the reference max moves
-// GUARD: a lane's sum of a tile's P past which the row maxima are looked for.
+// A lane's sum of a tile's P past which the pipelined loop moves the reference.
 // P up to about 2^16 is as exact as P <= 1, in bf16 and in the fp32 sums.
-constexpr float kGuardSum = 65536.f;
+constexpr float kFollowSum = 65536.f;
 // Instruction classes of __builtin_amdgcn_sched_group_barrier.
 constexpr int kSchedValu = 0x002;
 constexpr int kSchedMfma = 0x008;
@@ -169,13 +168,6 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
     float c /* scale * log2(e) */) {
   using C = FwdCfg<D, P>;
   constexpr int kStages = C::STAGES, kPD = C::PD;
-  // Whether the pipelined loop leaves the row maxima out and lets the row sums,
-  // which it needs anyway, say when the reference has been outgrown: 18 vector
-  // instructions less per tile.  Forward at S = 16K, 8 heads on 2: d = 64 340 ->
-  // 327 us, 96 395 -> 386, 80 360 -> 351.  At d = 128 the registers that the
-  // rare path needs are not there (230 spills, 0.5% slower), and with P = 2 K of
-  // the tile is gone by then.
-  constexpr bool kGuard = P == 1 && D < 128;
   using T = LdsTile<C::LW>;
   // LDS: the K tiles of the kStages ring stages, then their V tiles, so that
   // a stage's K and V tiles sit at the same offset from two fixed bases.
@@ -254,8 +246,8 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
       buf_load16_lds_async(rv, base + g_off[i], lds_off + kVRegion);
     }
   };
-  // P = 2: K and V apart.  Tile t's scores are formed one iteration before its
-  // P V, so K runs one tile ahead of V and two stages of each are enough.
+  // K or V of one tile.  P = 2: tile t's scores are formed one iteration before
+  // its P V, so K runs one tile ahead of V and two stages of each are enough.
   auto load_one = [&](int t, const RowView &view, u32x4 r, uint32_t region)
                       __attribute__((always_inline)) {
     uint32_t base = (uint32_t)(t * C::BT) * kv_row_bytes;
@@ -446,11 +438,10 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
   };
 
   // Tiles before t_mask need no mask.  They run software-pipelined: while
-  // the softmax of tile t (exponentials, conversions, row sum) is computed,
-  // the score products of tile t+1 are issued, and while P V of tile t runs,
-  // the row maxima of tile t+1 are formed, so that every stretch of the
-  // wave's instruction stream mixes matrix and vector work.  The arithmetic
-  // and its order per tile are those of `tile`: bit-identical results.
+  // the softmax of tile t (exponentials, conversions) is computed, the score
+  // products of tile t+1 are issued, and while P V of tile t runs, its row sum
+  // is formed, so that every stretch of the wave's instruction stream mixes
+  // matrix and vector work.
   const int t_mask = min(nt, q0 / C::BT);
   auto scores = [&](int t, f32x16 (&sc)[2]) __attribute__((always_inline)) {
     const unsigned char *Ks = smem + (t % kStages) * C::TILE_BYTES;
@@ -522,25 +513,22 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
         oacc[n] = mfma32x32x16(a, pf[s2], oacc[n]);
       }
   };
-  // kGuard, before P V of tile t: where a lane's sum says that the reference
-  // has been outgrown (or is no number: P overflowed, or a score is NaN) the
-  // tile's scores are formed again, K of tile t being still in its stage, and
-  // P after the reference moved as in `tile`.
-  auto guard = [&](int t, f32x16 (&cur)[2], bf16x8 (&pf)[kBN / 16], float &psum)
-                   __attribute__((always_inline)) {
-    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(psum <= kGuardSum)) != 0, 0)) {
+  // The pipelined loop forms no row maxima: the row sums, needed anyway, say
+  // when the reference has been outgrown, and it then follows them (half a
+  // row's sum is at least its maximum), 18 vector instructions less per tile.
+  // Should P have passed fp32's range before that, O or the row sum is no
+  // finite number in the end, and the rows are done over (below).
+  auto follow = [&](float psum) __attribute__((always_inline)) {
+    if (__builtin_amdgcn_ballot_w64(!(psum <= kFollowSum))) {  // wave-uniform, rare
       asm volatile("" ::: "memory");
-      const unsigned char *Ks = smem + (t % kStages) * C::TILE_BYTES;
+      const float up = fast_log2(fmaxf(pair_max(psum), 1.f));
+      const float alpha = fast_exp2(-up);
+      m_ref += up;
+      l_run *= alpha;
 #pragma unroll
-      for (int g = 0; g < 2 * C::NS; ++g) {
-        const bf16x8 a =
-            *reinterpret_cast<const bf16x8 *>(Ks + k_off[g / 2] + (g % 2) * 32 * T::ROW_BYTES);
-        cur[g % 2] = mfma32x32x16(a, qf[g / 2], g < 2 ? f32x16{} : cur[g % 2]);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      move_reference(row_max(cur));
-      exps(cur, pf);
-      psum = row_sum(cur);
+      for (int n = 0; n < C::NE; ++n)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) oacc[n][r] *= alpha;
     }
   };
   // Iteration t of the pipelined loop, tile t+1 unmasked: `cur` holds the
@@ -555,7 +543,6 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
     make_visible(min(1, nt - 2 - t), t + kPD + 1);  // tile t+1 readable, t+2 in flight
     asm volatile("" : "+v"(m_ref));  // keep the exponent arguments here
     bf16x8 pf[kBN / 16];
-    float psum = 0.f, mx = -INFINITY;
     // Block X: scores of tile t+1 (16 products), exponentials of tile t, at
     // raised issue priority: of the two waves of a SIMD, the one in this
     // block keeps the matrix unit while the other is in block Y.
@@ -580,7 +567,6 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
         for (int e = 32 * g / NG; e < 32 * (g + 1) / NG; ++e) {
           const int mm = e / 16, r = e % 16;
           cur[mm][r] = fast_exp2(fmaf(cur[mm][r], c, -m_ref));
-          if constexpr (kGuard) psum += cur[mm][r];
           if (r % 8 == 7) {
             const int b8 = r - 7;
             pf[2 * mm + b8 / 8] = as_bf16x8(u32x4{pack_bf16x2(cur[mm][b8 + 0], cur[mm][b8 + 1]),
@@ -593,8 +579,8 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
       }
     }
     wave_priority<0>();
-    // Block Y: P V of tile t (16 products), row sum of t, row maxima of t+1.
-    if constexpr (kGuard) guard(t, cur, pf, psum);
+    // Block Y: P V of tile t (16 products), row sum of t.
+    float psum = 0.f;
     {
       constexpr int NG = C::NE * (kBN / 16);
       const unsigned char *Vs = smem + ST * C::TILE_BYTES;
@@ -612,18 +598,13 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
         if (g + kPf < NG) read(g + kPf);
         const int n = g / (kBN / 16), s2 = g % (kBN / 16);
         oacc[n] = mfma32x32x16(op[g], pf[s2], oacc[n]);
-        if constexpr (!kGuard) {
 #pragma unroll
-          for (int e = 32 * g / NG; e < 32 * (g + 1) / NG; ++e) psum += cur[e / 16][e % 16];
-#pragma unroll
-          for (int e = 32 * g / NG; e < 32 * (g + 1) / NG; ++e) mx = fmaxf(mx, nxt[e / 16][e % 16]);
-        }
+        for (int e = 32 * g / NG; e < 32 * (g + 1) / NG; ++e) psum += cur[e / 16][e % 16];
         __builtin_amdgcn_sched_barrier(0);
       }
     }
     l_run += psum;
-    if constexpr (!kGuard)
-      move_reference(pair_max(mx) * c);  // after P V of tile t, before the exponentials of t+1
+    follow(psum);  // after P V of tile t, before the exponentials of t+1
   };
   // The last unmasked tile t: no scores to start.
   auto pipelined_last = [&](int t, f32x16 (&cur)[2]) __attribute__((always_inline)) {
@@ -631,14 +612,9 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
     asm volatile("" : "+v"(m_ref));
     bf16x8 pf[kBN / 16];
     exps(cur, pf);
-    float psum = 0.f;
-    if constexpr (kGuard) {
-      psum = row_sum(cur);
-      guard(t, cur, pf, psum);
-    }
     __builtin_amdgcn_sched_barrier(0);
     pv(t, pf);
-    if constexpr (!kGuard) psum = row_sum(cur);
+    const float psum = row_sum(cur);
     l_run += psum;
     __builtin_amdgcn_sched_group_barrier(kSchedDsRead, 4, 0);
 #pragma unroll
@@ -649,6 +625,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
     }
     __builtin_amdgcn_sched_group_barrier(kSchedMfma, 2, 0);
     __builtin_amdgcn_sched_barrier(0);
+    follow(psum);
   };
   if (t_mask > 0) {
     f32x16 sa[2], sb[2];
@@ -706,6 +683,33 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
   for (int t = t_mask; t < nt; ++t) {  // the diagonal band, masked
     make_visible(min(kPD, nt - 1 - t), t + kPD + 1);
     if (t * C::BT + kBN * part <= wrow0 + 31) tile(t, std::true_type{});  // wave-uniform
+  }
+
+  // A sum that is no finite number, in any row of the workgroup: P overflowed,
+  // or the inputs hold such numbers.  All rows are done over, tile by tile with
+  // the row maxima, so that P <= 2^8.
+  if (t_mask > 0) {
+    float z = 0.f * l_run;
+#pragma unroll
+    for (int n = 0; n < C::NE; ++n)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) z = fmaf(0.f, oacc[n][r], z);
+    if (__syncthreads_or(!(z == 0.f))) {
+      m_ref = -INFINITY;
+      l_run = 0.f;
+#pragma unroll
+      for (int n = 0; n < C::NE; ++n)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) oacc[n][r] = 0.f;
+      for (int t = 0; t < nt; ++t) {
+        barrier_no_fence();  // every wave is done with the stage
+        load_one(t, kv, rk, 0);
+        load_one(t, vv, rv, kVRegion);
+        wait_vmcnt<0>();
+        barrier_no_fence();
+        if (t * C::BT + kBN * part <= wrow0 + 31) tile(t, std::true_type{});  // wave-uniform
+      }
+    }
   }
 
   // oacc[n][r] = O^T[e = 32n + 8(r/4) + 4hh + r%4][query row] (unnormalised)
