@@ -17,6 +17,7 @@
  *   basp_unpack_add  the same for fp32 gradients, added into the shards
  *   basp_pack_qkv / basp_unpack_grads   a step's three packs, or its three
  *                  gradient unpacks, in one launch
+ *   basp_unpack_pack   the unpack of O and the pack of dO in one launch
  *   basp_attn_fwd_sharded / basp_attn_bwd_sharded   attention straight on
  *                  the shard buffers of the exchange (no pack/unpack pass)
  *   basp_a2a_pack / basp_a2a_unpack   the owner's side of the same exchanges:
@@ -165,6 +166,16 @@ int basp_pack_qkv(const void *const *q_shards, const void *const *k_shards,
                   const void *const *v_shards, void *q, void *k, void *v, int b,
                   int S, int H, int H_kv, int d, int G, int rank, basp_dtype dtype,
                   void *stream);
+
+/* The turn from forward to backward in one call, for a step whose dO is
+ * there by then: basp_unpack of src (O) into dst_shards, then basp_pack of
+ * src_shards (dO) into dst, n_heads each, bit for bit, as one launch under
+ * the conditions of basp_pack_qkv.  Neither may overlap the other's buffers.
+ * Errors: those of the two calls, checked before anything is launched. */
+int basp_unpack_pack(const void *src, void *const *dst_shards,
+                     const void *const *src_shards, void *dst, int b, int S,
+                     int n_heads, int d, int G, int rank, basp_dtype dtype,
+                     void *stream);
 
 /* The send side of the backward's last exchange in one call: basp_unpack of
  * dQ (n = H), then of dK and dV (n = H_kv), fp32, bit for bit, as one launch

@@ -27,7 +27,8 @@ STATUS = {
 }
 # Every symbol include/basp.h declares.
 EXPORTS = ("basp_status_str", "basp_group_of", "basp_validate", "basp_pack",
-           "basp_unpack", "basp_unpack_add", "basp_pack_qkv", "basp_unpack_grads", "basp_a2a_pack", "basp_a2a_unpack",
+           "basp_unpack", "basp_unpack_add", "basp_pack_qkv", "basp_unpack_pack",
+           "basp_unpack_grads", "basp_a2a_pack", "basp_a2a_unpack",
            "basp_a2a_pack_bf16", "basp_attn_fwd",
            "basp_attn_fwd_sharded", "basp_attn_bwd_workspace_bytes", "basp_attn_bwd",
            "basp_attn_bwd_noalloc", "basp_attn_bwd_sharded_workspace_bytes",
@@ -65,6 +66,7 @@ def lib() -> ctypes.CDLL:
     L.basp_unpack.argtypes = [vp, ctypes.POINTER(vp)] + [i] * 7 + [vp]
     L.basp_unpack_add.argtypes = [vp, ctypes.POINTER(vp)] + [i] * 6 + [vp]
     L.basp_pack_qkv.argtypes = [ctypes.POINTER(vp)] * 3 + [vp] * 3 + [i] * 8 + [vp]
+    L.basp_unpack_pack.argtypes = [vp] + [ctypes.POINTER(vp)] * 2 + [vp] + [i] * 7 + [vp]
     L.basp_unpack_grads.argtypes = [vp] * 3 + [ctypes.POINTER(vp)] * 3 + [i] * 7 + [vp]
     L.basp_a2a_pack.argtypes = [vp, vp] + [i] * 6 + [vp]
     L.basp_a2a_unpack.argtypes = [vp, vp] + [i] * 6 + [vp]
@@ -220,6 +222,25 @@ def pack_qkv(q_shards, k_shards, v_shards, rank: int, q=None, k=None, v=None):
                                _dev(v, "v", dt), b, Sg * G, H, H_kv, d, G, rank, _dtype_code(q),
                                _stream(q)), "basp_pack_qkv")
     return q, k, v
+
+
+def unpack_pack(local: torch.Tensor, shards, src_shards, rank: int, out: torch.Tensor):
+    """unpack of ``local`` into ``shards``, then pack of ``src_shards`` into ``out``, in one call
+    (one launch when G <= 16); all of one dtype and head count."""
+    G = len(shards)
+    b, Sg, n, d = shards[0].shape
+    dt = local.dtype
+    src = _table(src_shards, "src_shards", dt, G)
+    shape, device = shards[0].shape, local.device
+    if len(src_shards) != G:
+        raise ValueError("src_shards and shards differ in number")
+    for t in src_shards:
+        if t.shape != shape or t.device != device:
+            raise ValueError("shards differ in shape or device")
+    _check(lib().basp_unpack_pack(_dev(local, "local"), _table(shards, "shards", dt, G), src,
+                                  _dev(out, "out", dt), b, Sg * G, n, d, G, rank,
+                                  _dtype_code(local), _stream(local)), "basp_unpack_pack")
+    return out
 
 
 def unpack_grads(dq, dk, dv, dq_shards, dk_shards, dv_shards, rank: int):

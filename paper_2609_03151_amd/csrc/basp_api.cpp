@@ -357,6 +357,20 @@ int basp_pack_qkv(const void *const *q_shards, const void *const *k_shards,
   return hip_status(basp::launch_permute_batch(pc, 3, (hipStream_t)stream));
 }
 
+int basp_unpack_pack(const void *src, void *const *dst_shards, const void *const *src_shards,
+                     void *dst, int b, int S, int n_heads, int d, int G, int rank,
+                     basp_dtype dtype, void *stream) {
+  basp::PermCall pc[2];
+  bool empty = false;
+  int rc = prep_pack(false, false, const_cast<const void *const *>(dst_shards), src, b, S, n_heads,
+                     d, G, rank, dtype, &pc[0], &empty);
+  if (!rc) rc = prep_pack(true, false, src_shards, dst, b, S, n_heads, d, G, rank, dtype, &pc[1],
+                          &empty);
+  if (rc || empty) return rc;
+  (void)hipGetLastError();
+  return hip_status(basp::launch_permute_batch(pc, 2, (hipStream_t)stream));
+}
+
 int basp_unpack_grads(const float *dq, const float *dk, const float *dv, float *const *dq_shards,
                       float *const *dk_shards, float *const *dv_shards, int b, int S, int H,
                       int H_kv, int d, int G, int rank, void *stream) {

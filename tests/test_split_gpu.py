@@ -127,6 +127,24 @@ def test_forward_references_that_move(b, S, Hl, Hkl, d, peak):
     check_close("LSE", f(lse), f(ref[1]), max_abs=LSE_MAX_ABS, mean_abs=LSE_MAX_ABS)
 
 
+@pytest.mark.parametrize("b,S,n,d,G,dtype", [
+    (2, 512, 8, 64, 2, torch.bfloat16), (1, 96, 6, 3, 3, torch.bfloat16),  # 16- and 2-byte rows
+    (1, 340, 17, 20, 17, torch.float32), (1, 8192, 32, 128, 8, torch.bfloat16),  # G > 16: two launches
+])
+def test_unpack_pack_is_both_calls(b, S, n, d, G, dtype):
+    g = torch.Generator("cuda").manual_seed(S)
+    mk = lambda: [torch.randn((b, S // G, n, d), generator=g, device="cuda").to(dtype)
+                  for _ in range(G)]
+    src, rank = mk(), G - 1
+    local = torch.randn((b, S, n // G, d), generator=g, device="cuda").to(dtype)
+    want = basp.unpack(local, [torch.zeros_like(t) for t in src], rank)
+    got, out = [torch.zeros_like(t) for t in src], torch.empty_like(local)
+    basp.unpack_pack(local, got, src, rank, out=out)
+    torch.cuda.synchronize()
+    assert torch.equal(out, basp.pack(src, rank))
+    assert all(torch.equal(x, y) for x, y in zip(got, want))
+
+
 @pytest.mark.parametrize("S", [1024, 5120, 16384])
 @pytest.mark.parametrize("d", [64, 128])
 def test_split_forward_in_place(S, d):

@@ -1,11 +1,14 @@
 """The cut of the backward's key pass into row chunks and query-head parts: a
 host build of the library's own rule (bwd_chunks), checked over 31 sequence
 lengths x 4 batch sizes x 28 head layouts x 3 head dims, plain and under
-AddressSanitizer and UndefinedBehaviorSanitizer (host code only)."""
+AddressSanitizer and UndefinedBehaviorSanitizer (host code only); and the
+argument checks of basp_unpack_pack."""
+import ctypes
 import os
 
 import pytest
 
+import paper_2609_03151_amd as basp
 from test_host_logic import HIPCC, SAN_ENV, SAN_HIPCC, _build_run
 
 
@@ -16,3 +19,23 @@ def test_bwd_plan(tmp_path, sanitize):
                      SAN_HIPCC if sanitize else ["-O2"], env=SAN_ENV if sanitize else None)
     assert out.startswith("bwd plan ok")
     assert int(out.split()[-1]) == 31 * 4 * 28 * 3
+
+
+def test_unpack_pack_checks_both_calls():
+    """basp_unpack_pack reports what either of its two permutations would, before any launch."""
+    L = basp.lib()
+    tab = lambda base, n=2: (ctypes.c_void_p * n)(*[base + 0x1000 * j for j in range(n)])
+    ok, none, f32, bf16 = 0, None, 1, 0
+    call = lambda src, dst_t, src_t, dst, b=1, S=64, n=4, d=64, G=2, rank=0, dt=bf16: \
+        L.basp_unpack_pack(src, dst_t, src_t, dst, b, S, n, d, G, rank, dt, none)
+    a, t, u, c = 0x100000, tab(0x200000), tab(0x300000), 0x400000
+    assert call(a, t, u, c, b=0) == ok                    # empty: no pointer is inspected
+    assert call(none, none, none, none, S=0) == ok
+    assert call(a, t, none, c) == 1 and call(a, none, u, c) == 1    # NULL
+    assert call(none, t, u, c) == 1 and call(a, t, u, none) == 1
+    assert call(a, t, (ctypes.c_void_p * 2)(0x1000, None), c) == 1
+    assert call(a, t, u, c, S=63) == 2 and call(a, t, u, c, n=3) == 2   # SHAPE
+    assert call(a, t, u, c, n=1) == 2                     # a shared head is not unpacked
+    assert call(a, t, u, c, rank=2) == 3                  # RANK
+    assert call(a, t, u, c, dt=7) == 4                    # UNSUPPORTED
+    assert call(a, t, u, c + 1) == 5 and call(a + 2, t, u, c, dt=f32) == 5   # ALIGN
