@@ -150,8 +150,9 @@ struct BwdArgs {
 // ------------------------------------------------------ bwd_kv (dV and dK)
 // Key-stationary, dV and dK in one pass.  A workgroup of 8 waves, two per
 // SIMD, owns 128 keys of one kv head and sweeps 64-row query steps for the
-// unit's query heads of the GQA group (bwd_chunks says how many and why).  Wave w takes keys 32 (w % 4) .. +31 and the
-// 32-row half w / 4 of every step, and forms
+// unit's query heads of the GQA group (bwd_chunks says how many and why).
+// Wave w takes keys 32 (w % 4) .. +31 and the 32-row half w / 4 of every step,
+// and forms
 //   S^T = K Q^T and dP^T = V dO^T       (K of its keys in registers; V too
 //                                        below d = 128, else from LDS)
 //   P = exp2(S c - LSE2),  dS = P (dP - D)

@@ -35,8 +35,9 @@ struct FastDiv {
 
 // Work schedule of the key-stationary backward pass (dV and dK).  A key
 // tile is kKvKeys keys; the rows it needs, [k0, S), are cut at multiples of
-// the chunk (kv_chunk_rows(S), T key tiles long), and a unit is one (key
-// tile kt, row chunk ch) pair that writes its own partial sum.  Per
+// the chunk (T key tiles long; bwd_chunks picks it), and a unit is one (key
+// tile kt, row chunk ch) pair, for all query heads of the kv head or one part
+// of them, that writes its own partial sum.  Per
 // (sequence, kv head) there are kv_units(n, T) units for n row chunks: first
 // the units that start at their chunk's first row ("full"), chunk by chunk
 // (chunk ch has tiles 0 .. ch*T of them); then the diagonal units (key tile
@@ -44,9 +45,10 @@ struct FastDiv {
 // when S fills whole chunks; a partial last chunk's are shorter).  Units
 // whose tile lies past S, or whose rows are empty, do nothing.  Longer chunks
 // mean fewer partial sums to write and add, shorter ones more, smaller units
-// to balance; a quarter of the sequence, between 2048 and 8192 rows,
-// measured best.  Past S = 128K the cap grows with S so that there are at
-// most 16 chunks: the partial sums take (chunks x S) rows of workspace,
+// to balance.  kv_chunk_rows is the chunk of a share that fills the GPU with
+// units of all query heads: a quarter of the sequence, between 2048 and 8192
+// rows, measured best.  Past S = 128K the cap grows with S so that there are
+// at most 16 chunks: the partial sums take (chunks x S) rows of workspace,
 // which would otherwise grow with S squared.  Host-callable for checking.
 constexpr int kKvKeys = 128;
 constexpr int kKvMaxChunks = 16;
@@ -235,7 +237,7 @@ inline BwdChunks bwd_chunks_of(const AttnShape &s, int rows, int splits) {
 // the CUs beside the units, so a unit is about 2 `mean` steps, at least 8, from
 // a mean of 128 on 256 steps and from 512 on `mean` / 2.  Measured on MI355X,
 // backward, unit lengths in steps: 8 heads on 2 kv heads of 128, S = 4096 (mean
-// 33): 64 steps 128 us, 32 steps 133, 16 steps 145, uncut 318; 2 heads on 1, S =
+// 33): 64 steps 128 to 139 us, 32 steps 133 to 142, 16 steps 145, uncut 318; 2 heads on 1, S =
 // 8192 (33): 131, 140, -, 308; 4 on 1 of 64, S = 4096 (16): 32 steps 48, 16 steps
 // 53, 64 steps 57; 8 on 2, S = 16K (520): 256 steps 1536, 512 steps 1576.
 // Up to a mean of 256 rows are cut first, down to 256, then query heads: the
@@ -244,9 +246,9 @@ inline BwdChunks bwd_chunks_of(const AttnShape &s, int rows, int splits) {
 // heads 872 us, 4096 of four 885).  Chunks are of equal length: a short last one
 // is as many units as a long one (two sequences of 8564 rows, 7 heads on 1 of
 // 128, as 8192 + 372 rows of one head 970 us, as equal chunks of two heads 854).
-// Where the partial sums would need more than both one part per chunk of
-// kv_chunk_rows, the cut of old, and the static buffer of
-// basp_attn_bwd_noalloc hold, units are longer, at last that cut.
+// The partial sums may take what one part per chunk of kv_chunk_rows takes, or
+// the static buffer of basp_attn_bwd_noalloc if that is more; where they would
+// not fit, units take more query heads, at last that cut.
 inline BwdChunks bwd_chunks(const AttnShape &s) {
   const BwdChunks whole = bwd_chunks_of(s, kv_chunk_rows(s.S), 1);
   if (s.S < 1 || s.Hkl < 1) return whole;
@@ -271,14 +273,18 @@ inline BwdChunks bwd_chunks(const AttnShape &s) {
     heads = (int)((want + rows / 2) / rows < n_rep ? (want + rows / 2) / rows : n_rep);
   }
   if (heads < 1) heads = 1;
+  BwdChunks ck = bwd_chunks_of(s, rows, (n_rep + heads - 1) / heads);
   const size_t whole_floats = bwd_workspace_floats(s, whole);
   const size_t limit = whole_floats > BASP_NOALLOC_SCRATCH_BYTES / sizeof(float)
                            ? whole_floats : BASP_NOALLOC_SCRATCH_BYTES / sizeof(float);
-  for (;; ++heads) {
-    const BwdChunks ck = bwd_chunks_of(s, rows, (n_rep + heads - 1) / heads);
-    if (bwd_workspace_floats(s, ck) <= limit) return ck;
-    if (heads >= n_rep) return whole;
-  }
+  if (bwd_workspace_floats(s, ck) <= limit) return ck;
+  const size_t slot = 2 * (size_t)s.b * s.Hkl * s.S * s.d;
+  const size_t slots = limit > ck.part_offset_floats ? (limit - ck.part_offset_floats) / slot : 0;
+  const size_t splits = slots / ck.n;  // below ck.splits
+  if (splits < 1) return whole;
+  heads = (int)((n_rep + splits - 1) / splits);
+  ck.splits = (n_rep + heads - 1) / heads;
+  return ck;
 }
 
 // Row groups of 32 query rows among the 8 waves of a dQ workgroup (R = 8, 4
