@@ -39,9 +39,10 @@
 //     no per-tile address arithmetic.
 //   * the exponent reference of a row starts as its first tile's maximum and
 //     follows only when it has been outgrown, so that O is rescaled on few
-//     tiles: by 16 (in log2 units) in the pipelined loop, which sees it in the
-//     row sums, by 8 elsewhere, where the maxima are formed.  P <= 2^16 is as
-//     exact in bf16 and in the fp32 sums as P <= 1.
+//     tiles: by 8 (in log2 units) where the maxima are formed, before the
+//     exponentials; in the pipelined loop, which sees it in the row sums, once
+//     a lane's sum of a tile has passed 2^16, after that tile's products.  P
+//     above 1 is as exact in bf16 and in the fp32 sums as P <= 1.
 //   * tiles strictly below the workgroup's diagonal band run a loop without
 //     any masking code; band tiles are masked, and a wave skips band tiles
 //     past its last row.  The grid is one-dimensional, heaviest query tiles
@@ -70,8 +71,8 @@ constexpr int kThreads = 512;
 constexpr int kWaves = 8;
 constexpr int kBN = 64;           // keys per wave and tile
 constexpr float kRescaleSlack = 8.f;  // log2 headroom before the reference max moves
-// A lane's sum of a tile's P past which the pipelined loop moves the reference.
-// P up to about 2^16 is as exact as P <= 1, in bf16 and in the fp32 sums.
+// A lane's sum of a tile's P past which the pipelined loop moves the reference:
+// low enough for the row sums of many tiles, high enough to be rare.
 constexpr float kFollowSum = 65536.f;
 // Instruction classes of __builtin_amdgcn_sched_group_barrier.
 constexpr int kSchedValu = 0x002;
@@ -516,19 +517,22 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
   // The pipelined loop forms no row maxima: the row sums, needed anyway, say
   // when the reference has been outgrown, and it then follows them (half a
   // row's sum is at least its maximum), 18 vector instructions less per tile.
-  // Should P have passed fp32's range before that, O or the row sum is no
-  // finite number in the end, and the rows are done over (below).
+  // In the tile that outgrows it P can come near the end of fp32's range, up to
+  // 128 powers of two above the reference, so what was summed is scaled by
+  // 2^(-up/2) twice: 2^-up itself can lie below fp32's normal range, where the
+  // exp unit gives 0.  Where P passed the range, O or the row sum is no finite
+  // number from then on, and the rows are done over (below).
   auto follow = [&](float psum) __attribute__((always_inline)) {
     if (__builtin_amdgcn_ballot_w64(!(psum <= kFollowSum))) {  // wave-uniform, rare
       asm volatile("" ::: "memory");
       const float up = fast_log2(fmaxf(pair_max(psum), 1.f));
-      const float alpha = fast_exp2(-up);
+      const float half = fast_exp2(-0.5f * up);
       m_ref += up;
-      l_run *= alpha;
+      l_run = l_run * half * half;
 #pragma unroll
       for (int n = 0; n < C::NE; ++n)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) oacc[n][r] *= alpha;
+        for (int r = 0; r < 16; ++r) oacc[n][r] = oacc[n][r] * half * half;
     }
   };
   // Iteration t of the pipelined loop, tile t+1 unmasked: `cur` holds the

@@ -127,6 +127,43 @@ def test_forward_references_that_move(b, S, Hl, Hkl, d, peak):
     check_close("LSE", f(lse), f(ref[1]), max_abs=LSE_MAX_ABS, mean_abs=LSE_MAX_ABS)
 
 
+@pytest.mark.parametrize("b,S,Hl,d", [(8, 1024, 8, d) for d in (64, 80, 96, 128)]     # 128 rows
+                         + [(8, 2048, 7, d) for d in (64, 80, 96, 128)])              # 256
+def test_forward_jump_near_the_top_of_fp32(b, S, Hl, d):
+    """One key 87 to 89 units (126 to 128 powers of two) above the row's reference: P is finite
+    and so are its sums, but the factor that brings them to the new reference is below fp32's
+    normal range.  Keys 0 .. 127 score 0 exactly, so every row of a sequence jumps by the same
+    amount; a later key scores 1.4 below the jump.  The shards in place give the same bits."""
+    log(f"[split jump] b={b} S={S} Hl={Hl} d={d}")
+    G, rank = 2, 1
+    g = torch.Generator("cuda").manual_seed(S + d)
+    mk = lambda n: torch.randn((b, S, n, d), generator=g, device="cuda")
+    q, k, v, do = mk(Hl), mk(1), 0.25 * mk(1), mk(Hl)
+    k[:, :128] = 0.0
+    scale = 0.125
+    q[..., :2], k[..., :2] = 8.0, 0.0  # times the scale: a key's first two elements are its score
+    for beta, jump in enumerate((87.0, 87.4, 87.6, 88.0, 88.4, 88.6, 88.7, 89.0)):
+        for at, score in ((300, jump), (700, jump - 1.4)):
+            k[beta, at] = 0.0
+            k[beta, at, 0, 0] = score
+            k[beta, at, 0, 1] = score - float(torch.tensor(score).bfloat16())
+    q, k, v, do = (t.to(torch.bfloat16) for t in (q, k, v, do))
+    o, lse = basp.attn_fwd(q, k, v, scale=scale)
+    other = lambda t: torch.cat([torch.zeros_like(t), t], dim=2)  # rank 0's heads, rank 1's
+    shards = lambda t: [x.contiguous() for x in torch.chunk(other(t), G, dim=1)]
+    q_sh, k_sh, v_sh = shards(q), shards(k), shards(v)
+    o_sh = [torch.zeros_like(t) for t in q_sh]
+    lse_sh = basp.attn_fwd_sharded(q_sh, k_sh, v_sh, o_sh, rank, scale=scale)
+    torch.cuda.synchronize()
+    ref = _reference(q, k, v, do, scale)
+    f = lambda t: t.double().cpu().numpy()
+    check_close("O", f(o), f(ref[0]))
+    check_close("LSE", f(lse), f(ref[1]), max_abs=LSE_MAX_ABS, mean_abs=LSE_MAX_ABS)
+    got = torch.cat([t[:, :, Hl:] for t in o_sh], dim=1)
+    assert torch.equal(got.view(torch.int16), o.view(torch.int16))
+    assert torch.equal(lse_sh, lse)
+
+
 @pytest.mark.parametrize("b,S,n,d,G,dtype", [
     (2, 512, 8, 64, 2, torch.bfloat16), (1, 96, 6, 3, 3, torch.bfloat16),  # 16- and 2-byte rows
     (1, 340, 17, 20, 17, torch.float32), (1, 8192, 32, 128, 8, torch.bfloat16),  # G > 16: two launches
