@@ -78,7 +78,7 @@ typedef enum basp_status {
   BASP_ERR_RANK = 3,        /* rank outside [0, G)                           */
   BASP_ERR_UNSUPPORTED = 4, /* d, dtype, G or size outside what the kernels handle */
   BASP_ERR_ALIGN = 5,       /* pointer not aligned as documented             */
-  BASP_ERR_WORKSPACE = 6,   /* workspace smaller than the query reports      */
+  BASP_ERR_WORKSPACE = 6,   /* workspace smaller than the least documented   */
   BASP_ERR_HIP = 7,         /* a HIP launch failed                           */
   BASP_ERR_DP_FALLBACK = 8  /* micro-batch larger than the world (plain DP)  */
 } basp_status;
@@ -268,15 +268,19 @@ int basp_attn_fwd_sharded(const void *const *q_shards,
                           float *lse, int b, int S, int H, int H_kv, int d,
                           int G, int rank, float scale, void *stream);
 
-/* Bytes of device workspace basp_attn_bwd (and basp_attn_bwd_sharded) needs
- * for this share of the Sec. II-A attention backward: the per-row pair
- * (LSE, D_i = dO_i . O_i) of every local query head, and, when the key pass
+/* Bytes of device workspace with which basp_attn_bwd (and basp_attn_bwd_sharded)
+ * runs fastest for this share of the Sec. II-A attention backward: the per-row
+ * pair (LSE, D_i = dO_i . O_i) of every local query head, and, when the key pass
  * takes the rows of a key in more than one unit, fp32 partial sums of dK and
  * dV per unit.  Units are row chunks (2048 to 8192 rows; past S = 128K a
  * sixteenth of S, so never more than 16 chunks and a workspace linear in S)
  * of all query heads; shares too small to fill the GPU that way are cut finer
- * as long as that needs no more than BASP_NOALLOC_SCRATCH_BYTES.  0 for an
- * invalid shape, and for an empty one (b == 0 or S == 0), which needs none. */
+ * as long as that needs no more than BASP_NOALLOC_SCRATCH_BYTES.  So a shorter
+ * sequence can have more to report than a longer one; the entry points also take
+ * less, down to the sums of the row chunks of all query heads (chunks of a
+ * quarter of S in whole 128s, 2048 to 8192 rows, past S = 128K a sixteenth of S;
+ * none for a single chunk), and cut the work to fit.  0 for an invalid shape,
+ * and for an empty one (b == 0 or S == 0), which needs none. */
 size_t basp_attn_bwd_workspace_bytes(int b, int S, int H, int H_kv, int d,
                                      int G);
 
@@ -292,9 +296,10 @@ size_t basp_attn_bwd_workspace_bytes(int b, int S, int H, int H_kv, int d,
  * dq [b,S,H/G,d], dk/dv [b,S,Hkl,d] in fp32, each fully overwritten
  * (dk/dv sum over the rank's query heads sharing a kv head; with a kv head
  * shared by several members these are that member's part).  workspace:
- * device buffer of at least basp_attn_bwd_workspace_bytes(), 16-byte
- * aligned, contents ignored on entry and undefined on return.  Results are
- * deterministic (no atomics).
+ * device buffer of basp_attn_bwd_workspace_bytes() or more, 16-byte
+ * aligned, contents ignored on entry and undefined on return.  A smaller one
+ * (down to what that query's comment says) is slower and adds dK and dV in
+ * another order, else the same.  Results are deterministic (no atomics).
  * Errors: NULL, SHAPE, UNSUPPORTED, ALIGN, WORKSPACE, HIP. */
 int basp_attn_bwd(const void *q, const void *k, const void *v, const void *o,
                   const float *lse, const void *d_o, float *dq, float *dk,
@@ -308,7 +313,8 @@ int basp_attn_bwd(const void *q, const void *k, const void *v, const void *o,
 
 /* basp_attn_bwd for callers that cannot allocate device memory (code under
  * stream capture, allocation-free serving loops, harnesses that forbid
- * hipMalloc): the same computation and results, bit for bit, with the
+ * hipMalloc): the same computation and results, bit for bit (with a
+ * workspace of the size the query reports), with the
  * workspace taken from a static device buffer of BASP_NOALLOC_SCRATCH_BYTES
  * that the library holds on each GPU.  The first call on a GPU looks up that
  * buffer's address; no call allocates or frees anything.  Arguments as
@@ -331,8 +337,10 @@ int basp_attn_bwd_noalloc(const void *q, const void *k, const void *v,
  * Q) and dQ, dK, dV (fp32) are written into the rank's head slices of their
  * G shard buffers ([b, S/G, H, d] for dQ, [b, S/G, H_kv, d] for dK and dV);
  * other heads are untouched.  The result is bit for bit that of basp_pack
- * (of dO), basp_attn_bwd and basp_unpack of each gradient.  lse as there;
- * workspace of basp_attn_bwd_sharded_workspace_bytes(), 16-byte aligned
+ * (of dO), basp_attn_bwd and basp_unpack of each gradient, each with the
+ * workspace its query reports.  lse as there; workspace of
+ * basp_attn_bwd_sharded_workspace_bytes() (or less, as basp_attn_bwd takes,
+ * beyond the local copies), 16-byte aligned
  * (the rank's heads of Q, dO, K and V are first packed into it: the passes
  * stream those rows many times, and local rows stream faster than rows a
  * whole shard row apart).
@@ -344,7 +352,7 @@ int basp_attn_bwd_noalloc(const void *q, const void *k, const void *v,
  * dk, dv); member j sums the blocks of the sharing members in member order
  * (basp_a2a_unpack does this).
  * Errors: as basp_attn_fwd_sharded, plus WORKSPACE. */
-/* Bytes of device workspace basp_attn_bwd_sharded needs: local copies of
+/* Bytes of device workspace for basp_attn_bwd_sharded: local copies of
  * the rank's heads of Q and dO (each [b, S, H/G, d] bf16) and of K and V
  * (each [b, S, Hkl, d] bf16, Hkl as basp_attn_fwd), each rounded up to 256
  * bytes, then basp_attn_bwd_workspace_bytes().  0 for an invalid or empty

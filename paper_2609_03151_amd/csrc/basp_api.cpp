@@ -533,8 +533,8 @@ int basp_attn_bwd(const void *q, const void *k, const void *v, const void *o, co
   int rc = check_bwd_local(q, k, v, o, lse, d_o, dq, dk, dv, b, S, H, H_kv, d, G, scale, &empty);
   if (rc || empty) return rc;
   basp::AttnShape s = attn_shape(b, S, H, H_kv, d, G, scale);
-  const size_t need = basp::attn_bwd_workspace_bytes(s);
-  if (workspace_bytes < need) return BASP_ERR_WORKSPACE;
+  if (workspace_bytes < basp::attn_bwd_least_workspace_bytes(s)) return BASP_ERR_WORKSPACE;
+  s.workspace_bytes = workspace_bytes;
   if (!workspace) return BASP_ERR_NULL;
   if (!aligned(workspace, 16)) return BASP_ERR_ALIGN;
   return launch_bwd_local(q, k, v, o, lse, d_o, dq, dk, dv, workspace, s, stream);
@@ -551,6 +551,7 @@ int basp_attn_bwd_noalloc(const void *q, const void *k, const void *v, const voi
   if (basp::attn_bwd_workspace_bytes(s) > BASP_NOALLOC_SCRATCH_BYTES) return BASP_ERR_WORKSPACE;
   void *scratch = nullptr;
   if (basp::noalloc_scratch((hipStream_t)stream, &scratch) != hipSuccess) return BASP_ERR_HIP;
+  s.workspace_bytes = BASP_NOALLOC_SCRATCH_BYTES;
   return launch_bwd_local(q, k, v, o, lse, d_o, dq, dk, dv, scratch, s, stream);
 }
 
@@ -580,8 +581,9 @@ int basp_attn_bwd_sharded(const void *const *q_shards, const void *const *k_shar
   if (!aligned(lse, 4)) return BASP_ERR_ALIGN;
   basp::AttnShape s = attn_shape(b, S, H, H_kv, d, G, scale);
   const size_t copies = sharded_bwd_copies_bytes(s);
-  const size_t need = copies + basp::attn_bwd_workspace_bytes(s);
-  if (workspace_bytes < need) return BASP_ERR_WORKSPACE;
+  if (workspace_bytes < copies + basp::attn_bwd_least_workspace_bytes(s))
+    return BASP_ERR_WORKSPACE;
+  s.workspace_bytes = workspace_bytes - copies;
   if (!workspace) return BASP_ERR_NULL;
   if (!aligned(workspace, 16)) return BASP_ERR_ALIGN;
   // Q and dO rows are streamed once per key tile by the key-stationary pass,

@@ -185,6 +185,7 @@ hipError_t launch_cast_bf16(const float *const *src_tab, uint16_t *const *dst_ta
 struct AttnShape {
   int b, S, Hl, Hkl, d;  // local heads
   float scale;
+  size_t workspace_bytes = (size_t)-1;  // what the backward's cut has to fit
 };
 
 // `sharded`: the views may span several buffers (sequence shards whose row
@@ -247,8 +248,11 @@ inline BwdChunks bwd_chunks_of(const AttnShape &s, int rows, int splits) {
 // is as many units as a long one (two sequences of 8564 rows, 7 heads on 1 of
 // 128, as 8192 + 372 rows of one head 970 us, as equal chunks of two heads 854).
 // The partial sums may take what one part per chunk of kv_chunk_rows takes, or
-// the static buffer of basp_attn_bwd_noalloc if that is more; where they would
-// not fit, units take more query heads, at last that cut.
+// the static buffer of basp_attn_bwd_noalloc if that is more, and no more than
+// the workspace at hand holds; where they would not fit, units take more query
+// heads, then longer chunks, at last that cut.  A caller's buffer may be sized
+// for another, even a longer sequence, whose own cut needs less (8 heads on 2 of
+// 128: 61.6 MB at S = 3000, 33.8 MB at 4096).
 inline BwdChunks bwd_chunks(const AttnShape &s) {
   const BwdChunks whole = bwd_chunks_of(s, kv_chunk_rows(s.S), 1);
   if (s.S < 1 || s.Hkl < 1) return whole;
@@ -273,18 +277,27 @@ inline BwdChunks bwd_chunks(const AttnShape &s) {
     heads = (int)((want + rows / 2) / rows < n_rep ? (want + rows / 2) / rows : n_rep);
   }
   if (heads < 1) heads = 1;
-  BwdChunks ck = bwd_chunks_of(s, rows, (n_rep + heads - 1) / heads);
+  const BwdChunks best = bwd_chunks_of(s, rows, (n_rep + heads - 1) / heads);
+  auto fit = [&](size_t limit) {  // the cut in `limit` floats
+    BwdChunks ck = best;
+    if (bwd_workspace_floats(s, ck) <= limit) return ck;
+    const size_t slot = 2 * (size_t)s.b * s.Hkl * s.S * s.d;
+    const size_t slots = limit > ck.part_offset_floats ? (limit - ck.part_offset_floats) / slot : 0;
+    const size_t splits = slots / ck.n;  // below ck.splits
+    if (splits < 1) {
+      if (slots <= (size_t)whole.n) return whole;
+      return bwd_chunks_of(s, equal_rows((s.S + (long long)slots - 1) / (long long)slots), 1);
+    }
+    const int h = (int)((n_rep + splits - 1) / splits);
+    ck.splits = (n_rep + h - 1) / h;
+    return ck;
+  };
   const size_t whole_floats = bwd_workspace_floats(s, whole);
-  const size_t limit = whole_floats > BASP_NOALLOC_SCRATCH_BYTES / sizeof(float)
-                           ? whole_floats : BASP_NOALLOC_SCRATCH_BYTES / sizeof(float);
-  if (bwd_workspace_floats(s, ck) <= limit) return ck;
-  const size_t slot = 2 * (size_t)s.b * s.Hkl * s.S * s.d;
-  const size_t slots = limit > ck.part_offset_floats ? (limit - ck.part_offset_floats) / slot : 0;
-  const size_t splits = slots / ck.n;  // below ck.splits
-  if (splits < 1) return whole;
-  heads = (int)((n_rep + splits - 1) / splits);
-  ck.splits = (n_rep + heads - 1) / heads;
-  return ck;
+  const size_t most = whole_floats > BASP_NOALLOC_SCRATCH_BYTES / sizeof(float)
+                          ? whole_floats : BASP_NOALLOC_SCRATCH_BYTES / sizeof(float);
+  const BwdChunks ck = fit(most);
+  const size_t given = s.workspace_bytes / sizeof(float);
+  return bwd_workspace_floats(s, ck) <= given ? ck : fit(given);
 }
 
 // Row groups of 32 query rows among the 8 waves of a dQ workgroup (R = 8, 4
@@ -313,12 +326,19 @@ inline bool bwd_keys_first(const AttnShape &s, const BwdChunks &ck) {
   return unit * 1024 > 3LL * dq_row_groups(s) * s.S;
 }
 
-// Never less than the whole-chunk cut takes, which can be more than the one
-// in use: so what basp_attn_bwd_noalloc takes is what that cut lets it take.
-inline size_t attn_bwd_workspace_bytes(const AttnShape &s) {
-  const size_t cut = bwd_workspace_floats(s, bwd_chunks(s));
-  const size_t whole = bwd_workspace_floats(s, bwd_chunks_of(s, kv_chunk_rows(s.S), 1));
-  return (cut > whole ? cut : whole) * sizeof(float);
+// The least workspace the backward runs in: the whole-chunk cut's.
+inline size_t attn_bwd_least_workspace_bytes(const AttnShape &s) {
+  return bwd_workspace_floats(s, bwd_chunks_of(s, kv_chunk_rows(s.S), 1)) * sizeof(float);
+}
+
+// What the cut takes when the workspace does not limit it; never less than the
+// least (the whole-chunk cut can take more than the one in use), so
+// basp_attn_bwd_noalloc takes what that cut lets it take.
+inline size_t attn_bwd_workspace_bytes(AttnShape s) {
+  s.workspace_bytes = (size_t)-1;
+  const size_t cut = bwd_workspace_floats(s, bwd_chunks(s)) * sizeof(float);
+  const size_t least = attn_bwd_least_workspace_bytes(s);
+  return cut > least ? cut : least;
 }
 
 // Device address of the static scratch buffer of basp_attn_bwd_noalloc

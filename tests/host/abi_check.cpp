@@ -203,9 +203,30 @@ int main() {
   CHECK(basp_attn_bwd_workspace_bytes(1, 4095, 8, 2, 128, 2) == 0);
   CHECK(basp_attn_bwd_workspace_bytes(1, 0, 8, 2, 128, 2) == 0);  // empty: nothing needed
   float *fq = (float *)p[6], *fk = (float *)p[7], *fv = (float *)p[8];
-  EXPECT(basp_attn_bwd(p[0], p[1], p[2], p[3], lse, p[5], fq, fk, fv, p[9], need - 1, 1, 4096, 8,
+  // the least workspace: the two planes, and the sums of two row chunks of 2048
+  const size_t least = 2ull * 4 * 4096 * 4 + 2ull * 2 * 4096 * 128 * 4;
+  EXPECT(basp_attn_bwd(p[0], p[1], p[2], p[3], lse, p[5], fq, fk, fv, p[9], least - 1, 1, 4096, 8,
                        2, 128, 2, 0.1f, nullptr),
          BASP_ERR_WORKSPACE);
+  for (size_t bytes : {least, least + 1, need - 1, 2 * need}) {
+    EXPECT(basp_attn_bwd(p[0], p[1], p[2], p[3], lse, p[5], fq, fk, fv, p[9], bytes, 1, 4096, 8, 2,
+                         128, 2, 0.1f, nullptr),
+           BASP_OK);
+    CHECK(basp::g_attn.workspace_bytes == bytes);
+  }
+  // a buffer sized for the longest sequence takes every shorter one, whose own
+  // finest cut may ask for more
+  int more = 0;
+  for (int heads : {8, 7})
+    for (int S = 64; S <= (heads == 8 ? 4096 : 8192); S += 64) {
+      const int kv = heads == 8 ? 2 : 1;
+      const size_t longest = basp_attn_bwd_workspace_bytes(1, heads == 8 ? 4096 : 8192, heads, kv, 128, 1);
+      more += basp_attn_bwd_workspace_bytes(1, S, heads, kv, 128, 1) > longest;
+      EXPECT(basp_attn_bwd(p[0], p[1], p[2], p[3], lse, p[5], fq, fk, fv, p[9], longest, 1, S,
+                           heads, kv, 128, 1, 0.1f, nullptr),
+             BASP_OK);
+    }
+  CHECK(more > 0);
   EXPECT(basp_attn_bwd(p[0], p[1], p[2], p[3], lse, p[5], fq, fk, fv, nullptr, need, 1, 4096, 8,
                        2, 128, 2, 0.1f, nullptr),
          BASP_ERR_NULL);
@@ -261,10 +282,17 @@ int main() {
   CHECK(need_s == basp_attn_bwd_workspace_bytes(1, 4096, 8, 4, 128, 4) + 2ull * 4096 * 2 * 128 * 2 +
                       2ull * 4096 * 1 * 128 * 2);
   CHECK(basp_attn_bwd_sharded_workspace_bytes(0, 4096, 8, 4, 128, 4) == 0);
+  const size_t copies = need_s - basp_attn_bwd_workspace_bytes(1, 4096, 8, 4, 128, 4);
+  const size_t least_s = copies + 2ull * 2 * 4096 * 4 + 2ull * 2 * 4096 * 128 * 4;
   EXPECT(basp_attn_bwd_sharded(tq, tk, tv, to, lse, td, (float *const *)tdq, (float *const *)tdk,
-                               (float *const *)tdv, p[9], need_s - 16, 1, 4096, 8, 4, 128, 4, 1,
+                               (float *const *)tdv, p[9], least_s - 16, 1, 4096, 8, 4, 128, 4, 1,
                                0.1f, nullptr),
          BASP_ERR_WORKSPACE);
+  EXPECT(basp_attn_bwd_sharded(tq, tk, tv, to, lse, td, (float *const *)tdq, (float *const *)tdk,
+                               (float *const *)tdv, p[9], least_s, 1, 4096, 8, 4, 128, 4, 1,
+                               0.1f, nullptr),
+         BASP_OK);
+  CHECK(basp::g_attn.workspace_bytes == least_s - copies);
   EXPECT(basp_attn_bwd_sharded(tq, tk, tv, to, lse, td, (float *const *)tdq, (float *const *)tdk,
                                (float *const *)tdv, p[9], need_s, 1, 4096, 8, 4, 128, 4, 1, 0.1f,
                                nullptr),

@@ -8,7 +8,10 @@
 //    limit admits the same shapes), and no larger than both that and the
 //    static buffer;
 //  * the schedule of the chosen chunks reaches every (key tile, chunk) pair
-//    that has rows exactly once.
+//    that has rows exactly once;
+//  * in a workspace of any size from the least (one part per row chunk of
+//    kv_chunk_rows) up, the cut fits, and is the unlimited one from the size
+//    the query reports on.
 // Prints the number of shapes checked; exits 1 at the first failure.
 #include <stdio.h>
 
@@ -24,6 +27,23 @@ using namespace basp;
 static int fail(const char *what, const AttnShape &s) {
   printf("FAIL %s: b=%d S=%d Hl=%d Hkl=%d d=%d\n", what, s.b, s.S, s.Hl, s.Hkl, s.d);
   return 1;
+}
+
+// The cut in a workspace of `bytes`: whole chunks and parts that fit it.
+static const char *limited(AttnShape s, size_t bytes, const BwdChunks &best, size_t need) {
+  s.workspace_bytes = bytes;
+  const BwdChunks ck = bwd_chunks(s);
+  const int n_rep = s.Hl / s.Hkl;
+  if (ck.rows < kKvKeys || ck.T * kKvKeys != ck.rows || (long long)ck.n * ck.rows < s.S ||
+      (long long)(ck.n - 1) * ck.rows >= s.S || ck.n > kKvMaxChunks)
+    return "chunks in a small workspace";
+  if (ck.splits < 1 || ck.splits > n_rep) return "parts in a small workspace";
+  for (int p = 0; p < ck.splits; ++p)
+    if (p * n_rep / ck.splits >= (p + 1) * n_rep / ck.splits) return "empty part in a small one";
+  if (bwd_workspace_floats(s, ck) * sizeof(float) > bytes) return "cut larger than its workspace";
+  if (bytes >= need && (ck.rows != best.rows || ck.splits != best.splits))
+    return "another cut in a full workspace";
+  return nullptr;
 }
 
 int main() {
@@ -57,6 +77,14 @@ int main() {
             if (need < use || need < whole) return fail("workspace too small", s);
             if (need > std::max(whole, (size_t)BASP_NOALLOC_SCRATCH_BYTES) + 256)
               return fail("workspace too large", s);
+            if (attn_bwd_least_workspace_bytes(s) < whole ||
+                attn_bwd_least_workspace_bytes(s) > whole + 256)
+              return fail("least workspace", s);
+            const size_t least = attn_bwd_least_workspace_bytes(s);
+            for (size_t bytes : {least, least + 1, least + 2 * sum, (least + need) / 2,
+                                 least + (need - least) / 4 * 3, need - 1, need, 2 * need})
+              if (const char *what = bytes < least ? nullptr : limited(s, bytes, ck, need))
+                return fail(what, s);
             if (b == 1 && d == 64) {
               const int ktiles = (S + kKvKeys - 1) / kKvKeys;
               std::set<std::pair<int, int>> seen;

@@ -164,6 +164,37 @@ def test_forward_jump_near_the_top_of_fp32(b, S, Hl, d):
     assert torch.equal(lse_sh, lse)
 
 
+@pytest.mark.parametrize("b,S,Hl,Hkl,d,share", [
+    (1, 3000, 8, 2, 128, 0.55), (1, 3000, 8, 2, 128, 0.3), (1, 1024, 8, 1, 128, 0.6),
+    (2, 2048, 4, 1, 128, 0.5), (1, 1500, 8, 2, 128, 0.0), (2, 4100, 4, 1, 96, 0.0),
+])
+def test_backward_in_a_small_workspace(b, S, Hl, Hkl, d, share):
+    """A workspace below the size the query reports (the least, and between): the cut fits it,
+    nothing past its end is written, and the gradients hold."""
+    g = torch.Generator("cuda").manual_seed(S + d)
+    mk = lambda n: torch.randn((b, S, n, d), generator=g, device="cuda").to(torch.bfloat16)
+    q, k, v, do = mk(Hl), mk(Hkl), mk(Hkl), mk(Hl)
+    rows = max(2048, min(8192, S // 4 // 128 * 128))
+    least = 8 * b * Hl * ((S + 63) // 64 * 64)  # the planes, then one sum per row chunk
+    if S > rows:
+        least = (least + 255) // 256 * 256 + 8 * b * S * Hkl * d * ((S + rows - 1) // rows)
+    need = basp.attn_bwd_workspace_bytes(b, S, Hl, Hkl, d, 1)
+    n = (least + int(share * (need - least))) // 16 * 16
+    log(f"[split workspace] b={b} S={S} Hl={Hl} Hkl={Hkl} d={d}: {n} of {need} bytes")
+    assert n < need
+    o, lse = basp.attn_fwd(q, k, v)
+    ws = torch.full((need // 4 + 64,), math.nan, dtype=torch.float32, device="cuda")
+    ws[n // 4:] = 7.0
+    grads = [torch.full(t.shape, math.nan, dtype=torch.float32, device="cuda") for t in (q, k, v)]
+    basp.attn_bwd(q, k, v, o, lse, do, dq=grads[0], dk=grads[1], dv=grads[2],
+                  workspace=ws[:n // 4])
+    torch.cuda.synchronize()
+    assert bool((ws[n // 4:] == 7.0).all())
+    _, _, *ref = _reference(q, k, v, do, d ** -0.5)
+    for name, got, want in zip(("dQ", "dK", "dV"), grads, ref):
+        check_close(name, got.double().cpu().numpy(), want.cpu().numpy())
+
+
 @pytest.mark.parametrize("b,S,n,d,G,dtype", [
     (2, 512, 8, 64, 2, torch.bfloat16), (1, 96, 6, 3, 3, torch.bfloat16),  # 16- and 2-byte rows
     (1, 340, 17, 20, 17, torch.float32), (1, 8192, 32, 128, 8, torch.bfloat16),  # G > 16: two launches
