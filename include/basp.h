@@ -167,10 +167,11 @@ int basp_pack_qkv(const void *const *q_shards, const void *const *k_shards,
                   int S, int H, int H_kv, int d, int G, int rank, basp_dtype dtype,
                   void *stream);
 
-/* The turn from forward to backward in one call, for a step whose dO is
- * there by then: basp_unpack of src (O) into dst_shards, then basp_pack of
- * src_shards (dO) into dst, n_heads each, bit for bit, as one launch under
- * the conditions of basp_pack_qkv.  Neither may overlap the other's buffers.
+/* basp_unpack of src into dst_shards, then basp_pack of src_shards into dst,
+ * n_heads each, bit for bit, as one launch under the conditions of
+ * basp_pack_qkv: for a program that has two such tensors in hand at once (the
+ * O of one layer and the dO of another, say; the dO of the same layer follows
+ * from its O and is not there yet).  Neither may overlap the other's buffers.
  * Errors: those of the two calls, checked before anything is launched. */
 int basp_unpack_pack(const void *src, void *const *dst_shards,
                      const void *const *src_shards, void *dst, int b, int S,

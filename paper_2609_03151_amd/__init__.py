@@ -226,7 +226,7 @@ def pack_qkv(q_shards, k_shards, v_shards, rank: int, q=None, k=None, v=None):
 
 def unpack_pack(local: torch.Tensor, shards, src_shards, rank: int, out: torch.Tensor):
     """unpack of ``local`` into ``shards``, then pack of ``src_shards`` into ``out``, in one call
-    (one launch when G <= 16); all of one dtype and head count."""
+    (one launch when G <= 16); all of one dtype and head count, and no buffer of one in the other."""
     G = len(shards)
     b, Sg, n, d = shards[0].shape
     dt = local.dtype

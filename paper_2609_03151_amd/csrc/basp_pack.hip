@@ -135,7 +135,7 @@ __global__ __launch_bounds__(256) void permute_kernel(ShardTable src, ShardTable
 }
 
 // Up to kMaxBatch permutations in one launch (the Q, K, V packs of a step,
-// its three gradient unpacks, or the unpack of O with the pack of dO):
+// its three gradient unpacks, or an unpack with a pack):
 // workgroups [first[k], first[k+1]) run permutation k with its own tables,
 // geometry and mode, so small tensors do not each pay a launch and a ramp.
 constexpr int kMaxBatch = 3;

@@ -11,9 +11,8 @@ once, and chains the library calls:
   backward: pack(dO) -> attn_bwd -> unpack(dQ), unpack(dK), unpack(dV)
 
 (the three packs and the three gradient unpacks each as one call,
-pack_qkv / unpack_grads).  A whole step, whose dO is there from the start,
-runs unpack(O) and pack(dO) as one call too (unpack_pack): one launch of 3 to
-5 us less, a tenth of the smallest shares' steps.
+pack_qkv / unpack_grads).  A step is the forward, then the backward: dO is
+packed only after O has left, as in training, where dO follows from O.
 
 With fewer kv heads than members (H_kv < G, G divisible by H_kv) the rank
 holds one kv head shared by G/H_kv members, and its dK, dV are that head's
@@ -36,7 +35,7 @@ import torch
 from . import (attn_bwd, attn_bwd_sharded, attn_bwd_sharded_workspace_bytes,
                attn_bwd_workspace_bytes, attn_fwd,
                attn_fwd_sharded, heads_per_member, pack, pack_qkv, unpack, unpack_add,
-               unpack_grads, unpack_pack)
+               unpack_grads)
 
 
 class RankShare:
@@ -115,11 +114,8 @@ class RankShare:
         self.unpack_grads()
 
     def step(self):
-        self.pack_qkv()
-        self.attn_fwd()
-        unpack_pack(self.o, self.o_shards, self.do_shards, self.rank, out=self.do)
-        self.attn_bwd()
-        self.unpack_grads()
+        self.forward()
+        self.backward()
 
     # attention on the shard buffers in place
     def forward_sharded(self):

@@ -17,6 +17,7 @@ import pytest
 import torch
 
 import paper_2609_03151_amd as basp
+from paper_2609_03151_amd.share import RankShare
 from parity import LSE_MAX_ABS, MAX_ABS, check_close, fp64_kv_head, log
 
 pytestmark = pytest.mark.gpu
@@ -211,6 +212,26 @@ def test_unpack_pack_is_both_calls(b, S, n, d, G, dtype):
     torch.cuda.synchronize()
     assert torch.equal(out, basp.pack(src, rank))
     assert all(torch.equal(x, y) for x, y in zip(got, want))
+
+
+def test_step_with_d_o_in_the_send_buffers():
+    """dO = O in place (the loss half the sum of O squared): a step is forward(), then backward()."""
+    G, b, S, n, d, rank = 2, 1, 1024, 4, 64, 1
+    g = torch.Generator("cuda").manual_seed(3)
+    mk = lambda h: [torch.randn((b, S // G, h, d), generator=g, device="cuda").to(torch.bfloat16)
+                    for _ in range(G)]
+    q, k, v = mk(2 * n), mk(2), mk(2)
+    want, got = (RankShare(q, k, v, None, G=G, rank=rank) for _ in range(2))
+    for sh in (want, got):
+        sh.do_shards = sh.o_shards
+    want.forward()
+    torch.cuda.synchronize()
+    want.backward()
+    got.step()
+    torch.cuda.synchronize()
+    assert torch.equal(got.do, got.o) and bool(got.o.any())
+    for name in ("dq_shards", "dk_shards", "dv_shards"):
+        assert all(torch.equal(a, c) for a, c in zip(getattr(got, name), getattr(want, name)))
 
 
 @pytest.mark.parametrize("S", [1024, 5120, 16384])

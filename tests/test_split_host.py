@@ -1,14 +1,16 @@
 """The cut of the backward's key pass into row chunks and query-head parts: a
 host build of the library's own rule (bwd_chunks), checked over 31 sequence
 lengths x 4 batch sizes x 28 head layouts x 3 head dims, plain and under
-AddressSanitizer and UndefinedBehaviorSanitizer (host code only); and the
-argument checks of basp_unpack_pack."""
+AddressSanitizer and UndefinedBehaviorSanitizer (host code only); the
+argument checks of basp_unpack_pack; and the order of a share's step."""
 import ctypes
 import os
 
 import pytest
+import torch
 
 import paper_2609_03151_amd as basp
+from paper_2609_03151_amd import share
 from test_host_logic import HIPCC, SAN_ENV, SAN_HIPCC, _build_run
 
 
@@ -39,3 +41,43 @@ def test_unpack_pack_checks_both_calls():
     assert call(a, t, u, c, rank=2) == 3                  # RANK
     assert call(a, t, u, c, dt=7) == 4                    # UNSUPPORTED
     assert call(a, t, u, c + 1) == 5 and call(a + 2, t, u, c, dt=f32) == 5   # ALIGN
+
+
+def test_step_is_forward_then_backward(monkeypatch):
+    """A step sends O before it takes dO, so that a dO that lives in O's send buffers (the loss
+    half the sum of O squared) is the O of this step; and it goes through forward() and
+    backward(), which a subclass may extend."""
+    G, b, S, H, d = 2, 1, 8, 2, 64
+    mk = lambda: [torch.zeros(b, S // G, H, d, dtype=torch.bfloat16) for _ in range(G)]
+
+    def unpack(local, shards, rank):
+        for j, t in enumerate(shards):
+            t[:, :, rank] = local[:, j * S // G:(j + 1) * S // G, 0]
+
+    def pack(shards, rank, out):
+        out[:, :, 0] = torch.cat([t[:, :, rank] for t in shards], dim=1)
+
+    both = lambda local, shards, src, rank, out: (pack(src, rank, out), unpack(local, shards, rank))
+    for name, f in (("unpack", unpack), ("pack", pack), ("unpack_pack", both),
+                    ("pack_qkv", lambda *a, **k: None), ("unpack_grads", lambda *a: None),
+                    ("attn_fwd", lambda *a, out, **k: out.fill_(3.0)),
+                    ("attn_bwd", lambda *a, **k: None)):
+        monkeypatch.setattr(share, name, f, raising=False)
+    sh = share.RankShare(mk(), mk(), mk(), None, G=G, rank=1)
+    sh.do_shards = sh.o_shards
+    sh.step()
+    assert bool((sh.do == 3.0).all())
+
+    seen = []
+
+    class Traced(share.RankShare):
+        def forward(self):
+            seen.append("forward")
+            super().forward()
+
+        def pack_do(self):
+            seen.append("pack_do")
+            super().pack_do()
+
+    Traced(mk(), mk(), mk(), mk(), G=G, rank=0).step()
+    assert seen == ["forward", "pack_do"]
