@@ -861,7 +861,8 @@ __device__ __forceinline__ void bwd_dq_tile(const BwdArgs &a, int L, unsigned ch
 // us; 8 heads, b*S = 2 x 2K 291 -> 232 us; 16K and more: within 1%.
 template <int D, bool SH, int R>
 __global__ __launch_bounds__(kKvThreads, 1) void bwd_main_kernel(const BwdArgs a) {
-  static_assert(kKvThreads == kDqThreads, "one workgroup size for both passes");
+  static_assert(kKvThreads == kDqThreads && kKvThreads == kBwdThreads,
+                "one workgroup size for both passes");
   constexpr int kKvLds = KvCfg<D>::LDS_BYTES, kDqLds = DqCfg<D, R>::STAGES * DqCfg<D, R>::STAGE_BYTES;
   __shared__ __attribute__((aligned(16))) unsigned char smem[kKvLds > kDqLds ? kKvLds : kDqLds];
   const uint32_t kv_blocks = gridDim.x - a.dq_blocks;
@@ -909,11 +910,20 @@ hipError_t launch_bwd_d(const RowView &q, const RowView &k, const RowView &v, co
     a.dv = local_view(dv_part, s.S, s.Hkl, D);
     a.dk = local_view(dk_part, s.S, s.Hkl, D);
   }
+  const uint32_t dq_blocks = (uint32_t)bwd_dq_blocks(s), kv_blocks = (uint32_t)bwd_kv_blocks(s, ck);
   auto main_pass = [&](auto groups) {
     constexpr int R = decltype(groups)::value;
-    a.dq_blocks = (uint32_t)((s.S + 32 * R - 1) / (32 * R) * s.b * s.Hl);
-    const dim3 grid(a.dq_blocks + (unsigned)(ck.units * ck.splits * kvheads_total));
-    hipLaunchKernelGGL((bwd_main_kernel<D, SH, R>), grid, dim3(kKvThreads), 0, stream, a);
+    auto launch = [&](uint32_t of_dq, uint32_t of_kv) {
+      a.dq_blocks = of_dq;
+      hipLaunchKernelGGL((bwd_main_kernel<D, SH, R>), dim3(of_dq + of_kv), dim3(kKvThreads), 0,
+                         stream, a);
+    };
+    if (bwd_one_launch(s, ck)) {
+      launch(dq_blocks, kv_blocks);
+    } else {
+      launch(dq_blocks, 0);
+      launch(0, kv_blocks);
+    }
   };
   switch (dq_row_groups(s)) {
     case 2: main_pass(std::integral_constant<int, 2>{}); break;

@@ -326,6 +326,21 @@ inline bool bwd_keys_first(const AttnShape &s, const BwdChunks &ck) {
   return unit * 1024 > 3LL * dq_row_groups(s) * s.S;
 }
 
+// Workgroups of the two passes.  They go in one launch where its threads are a
+// 32-bit count, as a launch's have to be; past that (more than 2^23 - 1 heads and
+// kv heads of sequences of up to 256 rows, say) in one launch each.
+constexpr int kBwdThreads = 512;
+inline long long bwd_dq_blocks(const AttnShape &s) {
+  const int rows = 32 * dq_row_groups(s);
+  return (long long)((s.S + rows - 1) / rows) * s.b * s.Hl;
+}
+inline long long bwd_kv_blocks(const AttnShape &s, const BwdChunks &ck) {
+  return (long long)ck.units * ck.splits * s.b * s.Hkl;
+}
+inline bool bwd_one_launch(const AttnShape &s, const BwdChunks &ck) {
+  return (bwd_dq_blocks(s) + bwd_kv_blocks(s, ck)) * kBwdThreads <= 0xFFFFFFFFll;
+}
+
 // The least workspace the backward runs in: the whole-chunk cut's.
 inline size_t attn_bwd_least_workspace_bytes(const AttnShape &s) {
   return bwd_workspace_floats(s, bwd_chunks_of(s, kv_chunk_rows(s.S), 1)) * sizeof(float);

@@ -11,7 +11,9 @@
 //    that has rows exactly once;
 //  * in a workspace of any size from the least (one part per row chunk of
 //    kv_chunk_rows) up, the cut fits, and is the unlimited one from the size
-//    the query reports on.
+//    the query reports on;
+//  * no launch of the two passes has more than 2^32 - 1 threads, and both go in
+//    one where that allows it.
 // Prints the number of shapes checked; exits 1 at the first failure.
 #include <stdio.h>
 
@@ -46,7 +48,28 @@ static const char *limited(AttnShape s, size_t bytes, const BwdChunks &best, siz
   return nullptr;
 }
 
+// Shares at the limit of a launch: many short sequences (b up to 65535).
+static const char *launches(const AttnShape &s) {
+  const BwdChunks ck = bwd_chunks(s);
+  const long long dq = bwd_dq_blocks(s), kv = bwd_kv_blocks(s, ck), most = 0xFFFFFFFFll / kBwdThreads;
+  if (dq < 1 || kv < 1 || dq > most || kv > most) return "a pass past a launch's limit";
+  return bwd_one_launch(s, ck) == (dq + kv <= most) ? nullptr : "launches";
+}
+
 int main() {
+  for (int S : {1, 64, 128, 200, 256})
+    for (int b : {60000, 65535})
+      for (int Hl : {1, 64, 65, 100, 128}) {
+        if (S > 64 && Hl > 64) continue;  // bwd_pre's own limit
+        const AttnShape s{b, S, Hl, Hl, 64, 1.f};
+        if (const char *what = launches(s)) return fail(what, s);
+      }
+  {  // each pass alone within a launch's limit, both together not
+    const AttnShape s{65535, 1, 65, 65, 64, 1.f};
+    if (bwd_one_launch(s, bwd_chunks(s))) return fail("one launch too large", s);
+    const AttnShape t{65535, 1, 64, 64, 64, 1.f};
+    if (!bwd_one_launch(t, bwd_chunks(t))) return fail("one launch would do", t);
+  }
   std::vector<int> lengths = {1,    64,   127,  128,  129,  255,  256,  500,   512,   1000,  1024,
                               1500, 2047, 2048, 2049, 3000, 4096, 5000, 8191,  8192,  8193,  12345,
                               16384, 20000, 32768, 65536, 100000, 131072, 131200, 262144, 524289};

@@ -196,6 +196,22 @@ def test_backward_in_a_small_workspace(b, S, Hl, Hkl, d, share):
         check_close(name, got.double().cpu().numpy(), want.cpu().numpy())
 
 
+def test_backward_of_more_workgroups_than_one_launch_takes():
+    """65535 sequences of one token, 65 heads: each pass fits a launch, both together do not.
+    With one key P = 1, so O = V and dV = dO bit for bit, and dQ = dK = 0 up to rounding."""
+    b, H, d = 65535, 65, 64
+    log(f"[split launches] b={b} S=1 H={H} d={d}")
+    g = torch.Generator("cuda").manual_seed(1)
+    q, k, v, do = (torch.randn((b, 1, H, d), generator=g, device="cuda", dtype=torch.bfloat16)
+                   for _ in range(4))
+    o, lse = basp.attn_fwd(q, k, v)
+    grads = [torch.full(t.shape, math.nan, dtype=torch.float32, device="cuda") for t in (q, k, v)]
+    basp.attn_bwd(q, k, v, o, lse, do, dq=grads[0], dk=grads[1], dv=grads[2])
+    torch.cuda.synchronize()
+    assert torch.equal(o, v) and torch.equal(grads[2], do.float())
+    assert max(float(t.abs().max()) for t in grads[:2]) <= MAX_ABS
+
+
 @pytest.mark.parametrize("b,S,n,d,G,dtype", [
     (2, 512, 8, 64, 2, torch.bfloat16), (1, 96, 6, 3, 3, torch.bfloat16),  # 16- and 2-byte rows
     (1, 340, 17, 20, 17, torch.float32), (1, 8192, 32, 128, 8, torch.bfloat16),  # G > 16: two launches
