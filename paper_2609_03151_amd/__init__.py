@@ -126,11 +126,13 @@ def _table(tensors, name: str, dtype, n: int):
     kind = _table_types.get(n)
     if kind is None:
         kind = _table_types[n] = ctypes.c_void_p * n
-    for t in tensors:
+    ptrs = []
+    for t in tensors:  # once: the caller may pass an iterator
         if not (isinstance(t, torch.Tensor) and t.is_cuda and t.is_contiguous()
-                and t.dtype == dtype):  # _dev says which tensor, and why
-            return kind(*[_dev(t, f"{name}[{j}]", dtype) for j, t in enumerate(tensors)])
-    return kind(*[t.data_ptr() for t in tensors])
+                and t.dtype == dtype):
+            _dev(t, f"{name}[{len(ptrs)}]", dtype)  # raises: says which tensor, and why
+        ptrs.append(t.data_ptr())
+    return kind(*ptrs)
 
 
 def _dtype_code(t: torch.Tensor) -> int:

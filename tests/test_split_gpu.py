@@ -230,6 +230,25 @@ def test_unpack_pack_is_both_calls(b, S, n, d, G, dtype):
     assert all(torch.equal(x, y) for x, y in zip(got, want))
 
 
+def test_shards_from_an_iterator():
+    """The tables of V and of dV may come from iterators, which are walked once."""
+    G, rank = 2, 1
+    g = torch.Generator("cuda").manual_seed(4)
+    mk = lambda h, t: [torch.randn((1, 64, h, 64), generator=g, device="cuda").to(t) for _ in range(G)]
+    q, k, v = mk(4, torch.bfloat16), mk(2, torch.bfloat16), mk(2, torch.bfloat16)
+    assert all(torch.equal(a, c) for a, c in zip(basp.pack_qkv(q, k, iter(v), rank),
+                                                 basp.pack_qkv(q, k, v, rank)))
+    local = [torch.cat(t, dim=1)[:, :, :n].contiguous().float() for t, n in ((q, 2), (k, 1), (v, 1))]
+    want, got = ([mk(h, torch.float32) for h in (4, 2, 2)] for _ in range(2))
+    for w, x in zip(want, got):
+        for a, c in zip(w, x):
+            c.copy_(a)
+    basp.unpack_grads(*local, *want, rank)
+    basp.unpack_grads(*local, got[0], got[1], iter(got[2]), rank)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, c) for w, x in zip(want, got) for a, c in zip(w, x))
+
+
 def test_step_with_d_o_in_the_send_buffers():
     """dO = O in place (the loss half the sum of O squared): a step is forward(), then backward()."""
     G, b, S, n, d, rank = 2, 1, 1024, 4, 64, 1
