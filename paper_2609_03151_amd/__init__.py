@@ -232,10 +232,10 @@ def unpack_pack(local: torch.Tensor, shards, src_shards, rank: int, out: torch.T
     G = len(shards)
     b, Sg, n, d = shards[0].shape
     dt = local.dtype
-    src = _table(src_shards, "src_shards", dt, G)
-    shape, device = shards[0].shape, local.device
     if len(src_shards) != G:
         raise ValueError("src_shards and shards differ in number")
+    src = _table(src_shards, "src_shards", dt, G)
+    shape, device = shards[0].shape, local.device
     for t in src_shards:
         if t.shape != shape or t.device != device:
             raise ValueError("shards differ in shape or device")

@@ -2,7 +2,7 @@
 host build of the library's own rule (bwd_chunks), checked over 31 sequence
 lengths x 4 batch sizes x 28 head layouts x 3 head dims, plain and under
 AddressSanitizer and UndefinedBehaviorSanitizer (host code only); the
-argument checks of basp_unpack_pack; and the order of a share's step."""
+argument checks of basp_unpack_pack and its binding; and the order of a share's step."""
 import ctypes
 import os
 
@@ -41,6 +41,14 @@ def test_unpack_pack_checks_both_calls():
     assert call(a, t, u, c, rank=2) == 3                  # RANK
     assert call(a, t, u, c, dt=7) == 4                    # UNSUPPORTED
     assert call(a, t, u, c + 1) == 5 and call(a + 2, t, u, c, dt=f32) == 5   # ALIGN
+
+
+def test_unpack_pack_wants_as_many_sources_as_shards():
+    mk = lambda n: [torch.zeros(1, 32, 4, 64) for _ in range(n)]
+    local = torch.zeros(1, 64, 2, 64)
+    for n in (1, 3):
+        with pytest.raises(ValueError, match="number"):
+            basp.unpack_pack(local, mk(2), mk(n), 0, out=torch.zeros_like(local))
 
 
 def test_step_is_forward_then_backward(monkeypatch):
