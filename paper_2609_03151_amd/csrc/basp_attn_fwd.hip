@@ -30,9 +30,10 @@
 //     wave has just finished with, so two later tiles stay in flight.
 //   * tiles left of the diagonal band are software-pipelined inside each
 //     wave: the score products of tile t+1 are issued between the
-//     exponentials of tile t, and the row sum of t between the P V products
-//     of t, one product per slot with its operand read two slots ahead.  Every
-//     stretch of a wave's instruction stream thus mixes matrix and vector work.
+//     exponentials of tile t, and the row sum of t (and, on short sequences,
+//     the row maxima of t+1) between the P V products of t, one product per
+//     slot with its operand read two slots ahead.  Every stretch of a wave's
+//     instruction stream thus mixes matrix and vector work.
 //   * LDS holds the K tiles of the four ring stages, then their V tiles, and
 //     the pipelined loop is unrolled over the four stages: every operand
 //     address is a lane's fixed offset plus an instruction immediate, with
@@ -40,9 +41,10 @@
 //   * the exponent reference of a row starts as its first tile's maximum and
 //     follows only when it has been outgrown, so that O is rescaled on few
 //     tiles: by 8 (in log2 units) where the maxima are formed, before the
-//     exponentials; in the pipelined loop, which sees it in the row sums, once
-//     a lane's sum of a tile has passed 2^16, after that tile's products.  P
-//     above 1 is as exact in bf16 and in the fp32 sums as P <= 1.
+//     exponentials; in the pipelined loop of long sequences, which sees it in
+//     the row sums, once a lane's sum of a tile has passed 2^16, after that
+//     tile's products.  P above 1 is as exact in bf16 and in the fp32 sums as
+//     P <= 1.
 //   * tiles strictly below the workgroup's diagonal band run a loop without
 //     any masking code; band tiles are masked, and a wave skips band tiles
 //     past its last row.  The grid is one-dimensional, heaviest query tiles
@@ -162,7 +164,7 @@ __device__ __forceinline__ bool merge_parts(unsigned char *smem, int rg, int par
   return true;
 }
 
-template <int D, bool SH, int P>
+template <int D, bool SH, int P, bool FOLLOW>
 __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
     const RowView qv, const RowView kv, const RowView vv, const RowView ov,
     float *__restrict__ lse, int S, int Hl, int n_rep, int heads_total, int qtiles,
@@ -514,9 +516,10 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
         oacc[n] = mfma32x32x16(a, pf[s2], oacc[n]);
       }
   };
-  // The pipelined loop forms no row maxima: the row sums, needed anyway, say
-  // when the reference has been outgrown, and it then follows them (half a
-  // row's sum is at least its maximum), 18 vector instructions less per tile.
+  // With FOLLOW the pipelined loop forms no row maxima: the row sums, needed
+  // anyway, say when the reference has been outgrown, and it then follows them
+  // (half a row's sum is at least its maximum), 18 vector instructions less per
+  // tile for a check of the workgroup's rows at the end (follows_sums).
   // In the tile that outgrows it P can come near the end of fp32's range, up to
   // 128 powers of two above the reference, so what was summed is scaled by
   // 2^(-up/2) twice: 2^-up itself can lie below fp32's normal range, where the
@@ -583,8 +586,9 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
       }
     }
     wave_priority<0>();
-    // Block Y: P V of tile t (16 products), row sum of t.
-    float psum = 0.f;
+    // Block Y: P V of tile t (16 products), row sum of t, (no FOLLOW) row
+    // maxima of t+1.
+    float psum = 0.f, mx = -INFINITY;
     {
       constexpr int NG = C::NE * (kBN / 16);
       const unsigned char *Vs = smem + ST * C::TILE_BYTES;
@@ -604,11 +608,18 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
         oacc[n] = mfma32x32x16(op[g], pf[s2], oacc[n]);
 #pragma unroll
         for (int e = 32 * g / NG; e < 32 * (g + 1) / NG; ++e) psum += cur[e / 16][e % 16];
+        if constexpr (!FOLLOW) {
+#pragma unroll
+          for (int e = 32 * g / NG; e < 32 * (g + 1) / NG; ++e)
+            mx = fmaxf(mx, nxt[e / 16][e % 16]);
+        }
         __builtin_amdgcn_sched_barrier(0);
       }
     }
     l_run += psum;
-    follow(psum);  // after P V of tile t, before the exponentials of t+1
+    // After P V of tile t, before the exponentials of t+1.
+    if constexpr (FOLLOW) follow(psum);
+    else move_reference(pair_max(mx) * c);
   };
   // The last unmasked tile t: no scores to start.
   auto pipelined_last = [&](int t, f32x16 (&cur)[2]) __attribute__((always_inline)) {
@@ -629,7 +640,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
     }
     __builtin_amdgcn_sched_group_barrier(kSchedMfma, 2, 0);
     __builtin_amdgcn_sched_barrier(0);
-    follow(psum);
+    if constexpr (FOLLOW) follow(psum);
   };
   if (t_mask > 0) {
     f32x16 sa[2], sb[2];
@@ -692,7 +703,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_kernel(
   // A sum that is no finite number, in any row of the workgroup: P overflowed,
   // or the inputs hold such numbers.  All rows are done over, tile by tile with
   // the row maxima, so that P <= 2^8.
-  if (t_mask > 0) {
+  if (FOLLOW && t_mask > 0) {
     float z = 0.f * l_run;
 #pragma unroll
     for (int n = 0; n < C::NE; ++n)
@@ -1008,12 +1019,26 @@ int row_groups(const AttnShape &s) {
   return rows <= (s.d == 64 ? 106496 : 81920) ? 4 : 8;
 }
 
+// Whether the pipelined loop follows the row sums or forms the row maxima: a
+// few percent less time per tile against a check of O and the sums at the end of
+// the workgroup, where 256-row workgroups of d = 128 also lose to registers kept
+// in scratch around the loop.  Forward, us, maxima | sums, 240K rows in sequences
+// of S, 8 heads on 2: d = 128: S = 1024 100 | 108; 3000 187 | 195; 6000 340 | 341;
+// 8192 370 | 367; 32K 1783 | 1743.  d = 96: 1024 88 | 91; 4096 190.5 | 190.5; 6000 282 |
+// 278; 32K 1477 | 1428.  d = 80: 4096 180 | 182; 6000 268 | 265; 32K 1375 | 1327.  d =
+// 64: 2048 87.3 | 89.6; 3000 120.1 | 120.3; 4096 144 | 142; 32K 1118 | 1055.  128 rows:
+// d = 128: 2048 43.3 | 44.1; 4096 60.8 | 59.4; d = 96: 2048 34.6 | 35.2; 4096 50.3 | 48.8.
+bool follows_sums(const AttnShape &s, int R) {
+  return s.S > (R == 4 || s.d == 64 ? 3072 : s.d == 128 ? 6144 : 4608);
+}
+
 }  // namespace
 
 hipError_t launch_attn_fwd(const RowView &q, const RowView &k, const RowView &v,
                            const RowView &o, float *lse, const AttnShape &s, bool sharded,
                            hipStream_t stream) {
   const int R = row_groups(s);
+  const bool follow = follows_sums(s, R);
   const int qtiles = (s.S + 32 * R - 1) / (32 * R);
   const int heads_total = s.b * s.Hl;
   const long long blocks = (long long)qtiles * heads_total;
@@ -1031,9 +1056,11 @@ hipError_t launch_attn_fwd(const RowView &q, const RowView &k, const RowView &v,
       case 2: go(attn_fwd_split_kernel<D, SH, 2>); break;
       case 4:
         if constexpr (D == 64) go(attn_fwd_split_kernel<D, SH, 4>);
-        else go(attn_fwd_kernel<D, SH, 2>);
+        else go(follow ? attn_fwd_kernel<D, SH, 2, true> : attn_fwd_kernel<D, SH, 2, false>);
         break;
-      default: go(attn_fwd_kernel<D, SH, 1>); break;
+      default:
+        go(follow ? attn_fwd_kernel<D, SH, 1, true> : attn_fwd_kernel<D, SH, 1, false>);
+        break;
     }
   };
   auto by_dim = [&](auto sh) {

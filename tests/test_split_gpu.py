@@ -103,6 +103,9 @@ def test_split_attention_matches_fp64(b, S, Hl, Hkl, d):
     (1, 1000, 4, 1, 128), (2, 700, 2, 2, 64),   # 64 rows per workgroup
     (1, 5000, 8, 1, 128), (1, 5000, 8, 1, 80),  # 128
     (8, 2000, 7, 1, 64), (8, 2000, 7, 1, 80), (8, 2000, 7, 1, 96), (8, 2000, 7, 1, 128),  # 256
+    # sequences long enough for the loop without row maxima: 128 rows, then 256
+    (1, 9000, 8, 1, 96), (4, 7000, 5, 1, 64), (4, 7000, 5, 1, 80), (4, 7000, 5, 1, 96),
+    (4, 7000, 5, 1, 128),
 ])
 @pytest.mark.parametrize("peak", ["late", "early", "jumps"])
 def test_forward_references_that_move(b, S, Hl, Hkl, d, peak):
@@ -128,8 +131,11 @@ def test_forward_references_that_move(b, S, Hl, Hkl, d, peak):
     check_close("LSE", f(lse), f(ref[1]), max_abs=LSE_MAX_ABS, mean_abs=LSE_MAX_ABS)
 
 
-@pytest.mark.parametrize("b,S,Hl,d", [(8, 1024, 8, d) for d in (64, 80, 96, 128)]     # 128 rows
-                         + [(8, 2048, 7, d) for d in (64, 80, 96, 128)])              # 256
+@pytest.mark.parametrize("b,S,Hl,d", [
+    *((8, 1024, 8, d) for d in (64, 128)), *((8, 2048, 7, d) for d in (64, 128)),  # row maxima
+    *((8, 3584, 2, d) for d in (80, 96, 128)),      # row sums, 128 rows
+    *((8, 6656, 3, d) for d in (64, 80, 96, 128)),  # row sums, 256 rows
+])
 def test_forward_jump_near_the_top_of_fp32(b, S, Hl, d):
     """One key 87 to 89 units (126 to 128 powers of two) above the row's reference: P is finite
     and so are its sums, but the factor that brings them to the new reference is below fp32's
