@@ -768,7 +768,8 @@ struct SplitCfg {
   static constexpr int BM = 32 * R;  // query rows per workgroup
   static constexpr int BN = 32 * P;  // keys per tile
   static constexpr int TILE_BYTES = BN * LW * 2;
-  static constexpr int STAGES = 2 * TILE_BYTES > 32768 ? 2 : 4;  // 128 KB at 128-wide rows
+  // 128 KB of ring, but for 64-wide rows with R = 4: 64 KB, two workgroups a CU.
+  static constexpr int STAGES = 2 * TILE_BYTES > 32768 ? 2 : 4;
   static constexpr int LDS_BYTES = STAGES * 2 * TILE_BYTES;
   static constexpr int NS = D / 16;
   static constexpr int NE = DC / 32;
@@ -1003,20 +1004,38 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd_split_kernel(
 }
 
 // Row groups of a workgroup: 8 (attn_fwd_kernel, P = 1), 4 (P = 2; at d = 64
-// the split kernel) or 2 (the split kernel).  Up to the lines below, in W = b *
-// Hl * S query rows, 256-row workgroups, causal and so of very different
-// lengths, leave CUs idle; past them the wider workgroups' higher rate wins:
-// a K or V tile feeds more products.  Forward, us on MI355X for 8 | 4 | 2:
-// d = 128: W = 16K 45 | - | 22; 31K 146 | 93 | 76; 37K 339 | 221 | 216; 40K 370 |
-// 243 | 248; 56K 280 | 197 | 241; 75K 108 | 105 | 122; 87K 149 | 150 | 175; 183K 932 |
-// 954 | 1165.  d = 96: 81K 103 | 98 | 118; 108K 373 | 392 | 478.  d = 64, where
-// VALU work bounds both and two split workgroups fit a CU: 35K 127 | 87 | 68;
-// 43K 31 | 24 | 28; 76K 190 | 160 | 184; 107K 216 | 216 | 266; 115K 135 | 141 |
-// 185; 172K 274 | 261 | 358.
+// the split kernel) or 2 (the split kernel).  256-row workgroups, causal and so
+// of very different lengths, leave CUs idle on small shares; wider workgroups
+// have the higher rate: a K or V tile feeds more products.  The lines are where
+// the two meet, in two measures.
+// Long sequences: up to W = b * Hl * S query rows.  Forward, us on MI355X for 8 |
+// 4 | 2: d = 128: W = 16K 45 | - | 22; 31K 146 | 93 | 76; 37K 339 | 221 | 216; 40K
+// 370 | 243 | 248; 56K 280 | 197 | 241; 75K 108 | 105 | 122; 87K 149 | 150 | 175;
+// 183K 932 | 954 | 1165.  d = 96: 81K 103 | 98 | 118; 108K 373 | 392 | 478.  d = 64,
+// where VALU work bounds both and two workgroups of 128 rows fit a CU: 35K 127 |
+// 87 | 68; 43K 31 | 24 | 28; 76K 190 | 160 | 184; 107K 216 | 216 | 266; 115K 135 |
+// 141 | 185; 172K 274 | 261 | 358.
+// Short ones (many heads of them): a workgroup is mostly its start and end, so
+// what counts is how often the CUs are filled.  One filling (256 workgroups) up to
+// S = 512 and, as the tiles' lengths part, 3/16 to 1/4 workgroup more per row of S
+// past it, or, for 128 rows, two fillings where 256 rows take two as well.  d = 128,
+// 8 | 4 | 2, heads x S: 48 x 256 13 | 12 | 9.4, 92 x 256 13 | 13 | 16, 140 x 256 14 |
+// 19 | 25; 32 x 512 18 | 15 | 11, 38 x 512 19 | 16 | 17, 78 x 512 20 | 24 | 30; 22 x 1024
+// 28 | 22 | 20, 31 x 1024 29 | 25 | 28, 62 x 1024 35 | 39 | 58; 16 x 2048 47 | 33 | 31, 18
+// x 2048 48 | 35 | 43; 140 x 257 26 | 23 | 24.  Up to 128 rows all have one workgroup
+// per head and 8 is best (376 x 64 10.4 | 14 | 15), at d = 64 4 (7.5 | 7.0 | 9.8),
+// which there takes the whole range but one filling against two of S <= 256 (188 x
+// 129 7.3 | 8.3 | 13.8).
 int row_groups(const AttnShape &s) {
-  const long long rows = (long long)s.b * s.Hl * s.S;
-  if (rows <= 38400) return 2;
-  return rows <= (s.d == 64 ? 106496 : 81920) ? 4 : 8;
+  const long long heads = (long long)s.b * s.Hl, rows = heads * s.S;
+  const long long b2 = heads * ((s.S + 63) / 64), b4 = heads * ((s.S + 127) / 128),
+                  b8 = heads * ((s.S + 255) / 256);
+  if (s.S <= 128) return s.d == 64 ? 4 : 8;
+  const long long past = s.S > 512 ? s.S - 512 : 0;
+  if (rows <= 38400 && b2 <= 256 + past * (s.d == 64 ? 4 : 3) / 16) return 2;
+  if (s.d == 64) return rows <= 106496 && !(s.S <= 256 && b8 <= 256 && b4 > 256) ? 4 : 8;
+  const bool few = b4 <= 256 + past * (s.d == 128 ? 3 : 4) / 16 || (b8 > 256 && b4 <= 512);
+  return rows <= 81920 && few ? 4 : 8;
 }
 
 // Whether the pipelined loop follows the row sums or forms the row maxima: a

@@ -42,6 +42,9 @@ CASES = [  # b, S, Hl, Hkl, d
     # forward rows per workgroup: 64 | 128 and 128 | 256
     (1, 4800, 8, 2, 128), (1, 4801, 8, 2, 96), (1, 10240, 8, 2, 80), (1, 10241, 8, 2, 80),
     (2, 6656, 8, 4, 64), (2, 6657, 8, 4, 64), (160, 130, 4, 2, 128), (300, 128, 1, 1, 96),
+    # many short sequences: 256, 128 and 64 rows by how often they fill the GPU
+    (8, 512, 4, 2, 128), (33, 512, 1, 1, 128), (65, 512, 1, 1, 80), (35, 257, 4, 1, 96),
+    (188, 129, 1, 1, 64), (189, 128, 1, 1, 64), (50, 200, 4, 4, 64), (22, 1024, 1, 1, 96),
 ]
 
 
