@@ -1,19 +1,27 @@
-"""Parity of the attention forward when a row's maximum logit keeps growing.
+"""Parity of the attention when a row's maximum logit keeps growing.
 
 The forward keeps, per query row, an exponent reference that starts at the
-largest logit of the first key tile and moves only when a later 64-key tile
-holds a logit more than 8 above it (in log2 units); moving it rescales the
-running sum, the output accumulator and, through them, the LSE the backward
-uses.  With N(0,1) inputs at scale 1/sqrt(d) a row's maximum hardly grows
-after the first tile, so these tests use ``ramped_local`` inputs, whose
-logits rise along the sequence (Sec. II-A's softmax over long rows with a
-recency bias; the incoming gradient dO at a quarter of unit scale keeps dK
-and dV, which such concentrated attention enlarges, in the range of the other
-tests), and check on the host, from the inputs alone, that a stated
-fraction of (row, later tile) pairs crosses the threshold.  O, LSE, dQ, dK and
-dV are then compared element by element with the fp64 oracle at the usual
-bar, on small shapes and on one S = 4096 shape whose key pass runs in two
-row chunks (GQA 4).
+largest logit of the first keys and moves only when it has been outgrown;
+moving it rescales the running sum, the output accumulator and, through them,
+the LSE the backward uses.  It does so in two ways:
+
+* where the maxima are formed (the kernel of small shares, whose waves each take
+  32 keys of a tile with a reference of their own; diagonal tiles; the pipelined
+  loop of short sequences), when a tile's maximum is more than 8 above it (in
+  log2 units);
+* in the pipelined loop of long sequences, when half a row's sum of a tile of 64
+  keys has passed 2^16, for every row of the wave's 32.
+
+With N(0,1) inputs at scale 1/sqrt(d) a row's maximum hardly grows after the
+first tile, so these tests use ``ramped_local`` inputs, whose logits rise along
+the sequence (Sec. II-A's softmax over long rows with a recency bias; the
+incoming gradient dO at a quarter of unit scale keeps dK and dV, which such
+concentrated attention enlarges, in the range of the other tests), and check,
+from the inputs alone, that a stated share of (row, later tile) pairs, or of
+moves per row, moves it by the rule of the kernel that runs.  O, LSE, dQ, dK and dV are then compared
+element by element at the usual bar: small shapes, one of them with a key pass
+of many row chunks, with the fp64 oracle, shapes past the small-share lines with
+plain fp64 torch.
 """
 import math
 
@@ -22,50 +30,86 @@ import torch
 
 import oracle
 import paper_2609_03151_amd as basp
-from parity import LSE_MAX_ABS, check_close, log
+from parity import LSE_MAX_ABS, check_close, fp64_kv_head, log
 from synth_inputs import ramped_local
 
 pytestmark = pytest.mark.gpu
 
-TILE = 64          # keys per tile of the forward
-SLACK_LOG2 = 8.0   # the reference moves when a tile's maximum exceeds it by this
+SLACK_LOG2 = 8.0    # a tile's maximum this far above the reference moves it
+SUM_LOG2 = 16.0     # so does, in the pipelined loop, half a row's sum past 2 to this
+WAVE_ROWS = 32      # rows of a wave, which move together there
+RAMP = 24.0         # twice the rise of the other cases' logits: two moves in a long row
 
 
-def reference_moves(q, k, scale):
-    """(moves, pairs, rows moved twice or more) over every (sequence, head, row):
-    replays the reference rule on fp64 logits of the bf16 inputs, tile by tile."""
-    b, S, Hl, d = q.shape
-    n_rep = Hl // k.shape[2]
-    c = scale / math.log(2.0)
-    ntiles = (S + TILE - 1) // TILE
-    moves = pairs = multi = 0
-    keys = torch.arange(ntiles * TILE)
-    for bt in range(b):
+def _logits(q, k, scale, beta, h, n_rep, keys):
+    """Causal logits of one head in log2 units, fp64, padded with -inf to ``keys`` columns."""
+    S = q.shape[1]
+    s = torch.full((S, keys), float("-inf"), dtype=torch.float64, device=q.device)
+    s[:, :S] = (q[beta, :, h].double() @ k[beta, :, h // n_rep].double().T) * (scale / math.log(2.0))
+    rows = torch.arange(S, device=q.device)
+    return s.masked_fill_(torch.arange(keys, device=q.device)[None, :] > rows[:, None],
+                          float("-inf"))
+
+
+def _by_maxima(s, parts):
+    """(moves, pairs, moves of each row): key parts of 32 keys, each with its reference."""
+    S = s.shape[0]
+    tmax = s.reshape(S, -1, parts, 32).max(dim=3).values  # [row, tile, part]
+    ref = tmax[:, 0].clone()
+    count = torch.zeros(S, dtype=torch.int64, device=s.device)
+    pairs = 0
+    for t in range(1, tmax.shape[1]):
+        m = tmax[:, t]
+        later = torch.isfinite(m) & torch.isfinite(ref)
+        grow = later & (m > ref + SLACK_LOG2)
+        count += grow.sum(1)
+        pairs += int(later.sum())
+        ref = torch.where(grow | ~torch.isfinite(ref), m, ref)
+    return int(count.sum()), pairs, count
+
+
+def _by_sums(s, parts):
+    """The same in the pipelined loop: workgroups of 256 / parts rows, parts of 64 keys, the
+    tiles left of a workgroup's diagonal band."""
+    S, tile = s.shape[0], 64 * parts
+    rows = 256 // parts
+    # Lane l and l + 32 of a row hold keys 0-3 and 4-7 of every 8.
+    x = s.reshape(S, -1, parts, 8, 2, 4)
+    ref = x[:, 0].amax(dim=(2, 3, 4))  # [row, part]
+    q0 = torch.arange(S, device=s.device) // rows * rows
+    wave = torch.arange(S, device=s.device) // WAVE_ROWS
+    count = torch.zeros(S, dtype=torch.int64, device=s.device)
+    pairs = 0
+    for t in range(1, S // tile):
+        live = (t * tile < q0)[:, None]
+        up = torch.log2(torch.exp2(x[:, t] - ref[:, :, None, None, None]).sum(dim=(2, 4)).amax(2))
+        own = live & (up > SUM_LOG2)
+        together = torch.zeros((int(wave[-1]) + 1, parts), dtype=torch.int32, device=s.device)
+        together = together.index_add_(0, wave, own.int()) > 0
+        moved = live & together[wave] & (up > 0.0)
+        ref = torch.where(moved, ref + up, ref)
+        count += moved.sum(1)
+        pairs += int(live.sum()) * parts
+    return int(count.sum()), pairs, count
+
+
+def reference_moves(q, k, scale, rule, parts):
+    """(moves, pairs, rows moved twice or more) over every (sequence, head, row)."""
+    b, S, Hl, _ = q.shape
+    keys = (S + 127) // 128 * 128
+    total = [0, 0, 0]
+    for beta in range(b):
         for h in range(Hl):
-            Q = q[bt, :, h].double()
-            K = torch.zeros(ntiles * TILE, d, dtype=torch.float64)
-            K[:S] = k[bt, :, h // n_rep].double()
-            s = (Q @ K.T) * c
-            s.masked_fill_(keys[None, :] > torch.arange(S)[:, None], float("-inf"))
-            tmax = s.reshape(S, ntiles, TILE).max(dim=2).values
-            ref = tmax[:, 0].clone()
-            count = torch.zeros(S, dtype=torch.int64)
-            for t in range(1, ntiles):
-                live = torch.arange(S) >= t * TILE
-                grow = live & (tmax[:, t] > ref + SLACK_LOG2)
-                ref = torch.where(grow, tmax[:, t], ref)
-                count += grow.long()
-                pairs += int(live.sum())
-            moves += int(count.sum())
-            multi += int((count >= 2).sum())
-    return moves, pairs, multi
+            moves, pairs, count = rule(_logits(q, k, scale, beta, h, Hl // k.shape[2], keys), parts)
+            total = [total[0] + moves, total[1] + pairs, total[2] + int((count >= 2).sum())]
+    return total
 
 
 CASES = [  # b, S, Hl, Hkl, d, least fraction of (row, later tile) pairs that move
-    (1, 1000, 4, 2, 128, 0.05),   # ragged tail, GQA 2 (8.1% move)
-    (2, 777, 2, 1, 64, 0.10),     # d = 64, b = 2, ragged (15.6%)
-    (1, 1200, 3, 1, 96, 0.05),    # d = 96, GQA 3 (8.6%)
-    (1, 4096, 4, 1, 128, 0.015),  # key pass in two row chunks, GQA 4 (2.1%)
+    (1, 1000, 4, 2, 128, 0.05),   # ragged tail, GQA 2 (15% move)
+    (2, 777, 2, 1, 64, 0.10),     # d = 64, b = 2, ragged (31%)
+    (1, 1200, 3, 1, 96, 0.05),    # d = 96, GQA 3 (17%)
+    (1, 4096, 4, 1, 128, 0.015),  # key pass in eight row chunks, GQA 4 (4.4%)
 ]
 
 
@@ -74,12 +118,12 @@ def test_moving_reference_matches_oracle(b, S, Hl, Hkl, d, frac):
     log(f"[rescale] b={b} S={S} Hl={Hl} Hkl={Hkl} d={d}")
     q, k, v, do = ramped_local(b, S, Hl, Hkl, d, seed=S + d)
     scale = 1.0 / math.sqrt(d)
-    moves, pairs, multi = reference_moves(q, k, scale)
+    qd, kd, vd, dod = (x.cuda() for x in (q, k, v, do))
+    moves, pairs, multi = reference_moves(qd, kd, scale, _by_maxima, 4)
     log(f"  reference moves: {moves} of {pairs} (row, later tile) pairs "
         f"({moves / pairs:.3%}); rows moved at least twice: {multi}")
     assert moves >= frac * pairs, "inputs do not exercise the moving reference"
     assert multi > 0
-    qd, kd, vd, dod = (x.cuda() for x in (q, k, v, do))
     o, lse = basp.attn_fwd(qd, kd, vd, G=1, scale=scale)
     dq, dk, dv = basp.attn_bwd(qd, kd, vd, o, lse, dod, G=1, scale=scale)
     torch.cuda.synchronize()
@@ -91,6 +135,43 @@ def test_moving_reference_matches_oracle(b, S, Hl, Hkl, d, frac):
     check_close("dQ", f64(dq), rdq)
     check_close("dK", f64(dk), rdk)
     check_close("dV", f64(dv), rdv)
+
+
+LONG = [  # b, S, Hl, Hkl, d, key parts of a workgroup
+    (1, 5120, 8, 2, 128, 2), (2, 3600, 6, 2, 80, 2), (1, 8200, 6, 1, 96, 2),  # 128 rows
+    (4, 3400, 8, 2, 64, 1), (4, 5000, 5, 1, 80, 1), (4, 5000, 5, 5, 96, 1),   # 256 rows
+    (3, 7200, 4, 1, 128, 1),
+]
+
+
+@pytest.mark.parametrize("b,S,Hl,Hkl,d,parts", LONG)
+def test_reference_that_follows_the_sums(b, S, Hl, Hkl, d, parts):
+    log(f"[rescale sums] b={b} S={S} Hl={Hl} Hkl={Hkl} d={d}")
+    q, k, v, do = (x.cuda() for x in ramped_local(b, S, Hl, Hkl, d, seed=S + d, ramp=RAMP,
+                                                     do_std=0.125))
+    scale = 1.0 / math.sqrt(d)
+    moves, pairs, multi = reference_moves(q, k, scale, _by_sums, parts)
+    rows = b * Hl * S
+    log(f"  reference moves: {moves} of {pairs} (row, later tile) pairs, {moves / rows:.3f} a row; "
+        f"rows moved at least twice: {multi / rows:.3f}")
+    assert moves >= 0.5 * rows and multi >= 0.2 * rows, "the reference is not exercised"
+    o, lse = basp.attn_fwd(q, k, v, scale=scale)
+    dq, dk, dv = basp.attn_bwd(q, k, v, o, lse, do, scale=scale)
+    torch.cuda.synchronize()
+    n = Hl // Hkl
+    f64 = lambda t: t.double().cpu().numpy()
+    for beta in range(b):
+        at = slice(beta, beta + 1)
+        for h in range(Hkl):
+            hq, hk = slice(h * n, (h + 1) * n), slice(h, h + 1)
+            ref = fp64_kv_head(q[at, :, hq], k[at, :, hk], v[at, :, hk], do[at, :, hq], n, scale)
+            got = o[beta, :, hq], dq[beta, :, hq], dk[beta, :, h], dv[beta, :, h]
+            for name, x, want in zip(("O", "dQ", "dK", "dV"), got, ref):
+                check_close(name, f64(x), f64(want))
+            for g in range(h * n, (h + 1) * n):
+                s = _logits(q, k, scale, beta, g, n, S) * math.log(2.0)
+                check_close("LSE", f64(lse[beta, g]), f64(torch.logsumexp(s, dim=1)),
+                            max_abs=LSE_MAX_ABS, mean_abs=LSE_MAX_ABS)
 
 
 def test_moving_reference_in_place_path_is_bitwise_the_same():
