@@ -12,6 +12,7 @@
 //  * in a workspace of any size from the least (one part per row chunk of
 //    kv_chunk_rows) up, the cut fits, and is the unlimited one from the size
 //    the query reports on;
+//  * the shapes of the GPU tests are cut the way those tests mean to run;
 //  * no launch of the two passes has more than 2^32 - 1 threads, and both go in
 //    one where that allows it.
 // Prints the number of shapes checked; exits 1 at the first failure.
@@ -56,7 +57,32 @@ static const char *launches(const AttnShape &s) {
   return bwd_one_launch(s, ck) == (dq + kv <= most) ? nullptr : "launches";
 }
 
+// Local shapes of the GPU tests whose cases stand for a cut: row chunks, parts.
+struct Meant {
+  int b, S, Hl, Hkl, d, n, splits;
+};
+const Meant kMeant[] = {
+    // without a workspace argument; in place; moving references
+    {1, 4096, 4, 1, 128, 8, 1}, {2, 1000, 2, 2, 64, 2, 1}, {3, 320, 2, 2, 64, 1, 1},
+    {1, 1024, 2, 1, 128, 4, 1}, {2, 4096, 4, 2, 64, 2, 1}, {2, 4096, 4, 4, 64, 1, 1},
+    {2, 8192, 1, 1, 128, 2, 1}, {1, 2048, 2, 1, 128, 8, 1}, {2, 4096, 2, 1, 64, 4, 1},
+    {16, 2048, 1, 1, 64, 1, 1},
+    // small shapes against the oracle; the long sequence at the cap of 16 chunks
+    {1, 2500, 2, 1, 128, 10, 1}, {1, 4096, 4, 2, 64, 4, 1}, {1, 2500, 2, 1, 80, 10, 1},
+    {2, 2112, 4, 2, 128, 4, 2}, {1, 4160, 7, 1, 64, 9, 1}, {1, 131200, 1, 1, 64, 16, 1},
+    // cuts of small shares
+    {1, 1024, 8, 1, 128, 4, 4}, {1, 1100, 7, 1, 96, 5, 4}, {2, 2048, 4, 1, 128, 8, 1},
+    {1, 3000, 7, 1, 128, 12, 1}, {3, 769, 6, 2, 80, 4, 2}, {1, 2113, 3, 3, 64, 5, 1},
+    {1, 6000, 10, 2, 64, 3, 1}, {1, 8192, 8, 2, 64, 2, 1}, {1, 8192, 8, 8, 64, 1, 1},
+    {2, 9000, 10, 2, 128, 2, 2}, {1, 11008, 20, 1, 64, 2, 7},
+};
+
 int main() {
+  for (const Meant &m : kMeant) {
+    const AttnShape s{m.b, m.S, m.Hl, m.Hkl, m.d, 1.f};
+    const BwdChunks ck = bwd_chunks(s);
+    if (ck.n != m.n || ck.splits != m.splits) return fail("another cut than its test means", s);
+  }
   for (int S : {1, 64, 128, 200, 256})
     for (int b : {60000, 65535})
       for (int Hl : {1, 64, 65, 100, 128}) {

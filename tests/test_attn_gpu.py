@@ -55,14 +55,14 @@ SMALL = [  # b, S, Hl, Hkl, d
     (1, 77, 2, 2, 128),      # shorter than one tile
     (1, 1, 2, 1, 64),        # a single token
     (1, 2048, 4, 1, 128),    # 16 row tiles, 32 key tiles
-    (1, 2500, 2, 1, 128),    # dK/dV rows split into 2 chunks, ragged tail
-    (1, 4096, 4, 2, 64),     # 2 chunks, d = 64
+    (1, 2500, 2, 1, 128),    # dK/dV rows in 10 chunks, ragged tail
+    (1, 4096, 4, 2, 64),     # 4 chunks, d = 64
     (1, 384, 8, 2, 96),      # d = 96 (Table II: 3072 / 32), GQA 4
     (1, 1000, 4, 1, 96),     # d = 96, ragged tail
-    (2, 300, 3, 3, 80),      # d = 80 (Table II: 2560 / 32), computed at 96, ragged
-    (1, 2500, 2, 1, 80),     # d = 80, 2 chunks, ragged tail
-    (2, 2112, 4, 2, 128),    # 2 chunks, the second one 64-row step; GQA 2, b = 2
-    (1, 4160, 7, 1, 64),     # 3 chunks (4160 = 2*2048 + 64), GQA 7, d = 64
+    (2, 300, 3, 3, 80),      # d = 80 (Table II: 2560 / 32), outputs computed at 96, ragged
+    (1, 2500, 2, 1, 80),     # d = 80, 10 chunks, ragged tail
+    (2, 2112, 4, 2, 128),    # 4 chunks x 2 query-head parts, GQA 2, b = 2
+    (1, 4160, 7, 1, 64),     # 9 chunks, the last one 64-row step; GQA 7, d = 64
 ]
 
 

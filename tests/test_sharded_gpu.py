@@ -55,8 +55,9 @@ def _compare_shares(ref: RankShare, got: RankShare, grads: bool = True):
 
 
 CASES = [  # b, S, H, H_kv, d, G, rank
-    (1, 1024, 8, 4, 128, 4, 1),     # one row chunk: dK/dV written by the key passes
-    (2, 4096, 8, 4, 64, 2, 1),      # two row chunks: dK/dV written by the reduction
+    (1, 1024, 8, 4, 128, 4, 1),     # four row chunks: dK/dV written by the reduction
+    (2, 4096, 8, 4, 64, 2, 1),      # two row chunks
+    (2, 4096, 8, 8, 64, 2, 1),      # one: dK/dV written by the key pass
     (1, 2048, 12, 4, 96, 4, 3),     # d = 96, one kv head per member
     (1, 3072, 8, 8, 80, 4, 2),      # d = 80, 768 rows per shard
     (2, 1536, 6, 6, 128, 6, 5),     # G = 6
@@ -79,8 +80,9 @@ def test_sharded_step_equals_composed_bitwise(b, S, H, H_kv, d, G, rank):
 
 
 SHARED = [  # b, S, H, H_kv, d, G, rank: a kv head shared by G / H_kv members
-    (1, 2048, 16, 4, 128, 8, 3),    # one row chunk
-    (2, 4096, 8, 2, 64, 4, 1),      # two row chunks, b = 2
+    (1, 2048, 16, 4, 128, 8, 3),    # eight row chunks
+    (2, 4096, 8, 2, 64, 4, 1),      # four row chunks, b = 2
+    (16, 2048, 4, 2, 64, 4, 2),     # one: dK/dV written by the key pass
     (1, 4096, 16, 8, 96, 16, 9),    # G = 16, 2 members per kv head
     (1, 16384, 64, 8, 128, 64, 37), # G = 64: Llama-3-70B heads, 8 members per kv head
 ]

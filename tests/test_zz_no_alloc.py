@@ -1,6 +1,6 @@
 """basp_attn_bwd_noalloc (the backward without a workspace argument, for
-callers that cannot allocate) against basp_attn_bwd on the same inputs: two
-calls in a row on one GPU, the second with a smaller input, each bit for bit
+callers that cannot allocate) against basp_attn_bwd on the same inputs: calls
+in a row on one GPU, each with a smaller input than the one before, bit for bit
 equal to the workspace entry point's dQ, dK, dV (the same kernels in the same
 order), with NaN-filled outputs so that every element must be written."""
 import math
@@ -13,9 +13,10 @@ from parity import log
 
 pytestmark = pytest.mark.gpu
 
-CALLS = [  # b, S, Hl, Hkl, d: key pass in two row chunks, then one chunk, ragged
-    (1, 4096, 4, 1, 128),
-    (2, 1000, 2, 2, 64),
+CALLS = [  # b, S, Hl, Hkl, d
+    (1, 4096, 4, 1, 128),   # key pass in eight row chunks
+    (2, 1000, 2, 2, 64),    # two, ragged
+    (3, 320, 2, 2, 64),     # one: the key pass writes dK and dV, nothing is added up
 ]
 
 
